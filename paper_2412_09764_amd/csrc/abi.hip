@@ -400,14 +400,19 @@ static int search_common(const char* fn, const void* q, pkmem_dtype q_dt, const 
     if (e != hipSuccess) return hip_status(e, fn);
   }
   int32_t* hidx = half_idx_out ? half_idx_out : w.half_idx;
-  e = pk::launch_search_half(bf16, q, subkeys, T, H, n, S, k, qstats, has_sink ? sink : nullptr,
-                             w.sink_part, w.cand, w.cnts, w.thr, hidx, w.half_score, w.ovf, st);
+  pk::SplitPlan plan{0, 0, 0, 0};  // parts = 0: half lists, no part records
+  if (pk::split_plan(bf16, T, H, S, k, &plan))
+    e = pk::launch_search_split(bf16, q, subkeys, T, H, n, S, k, qstats, has_sink ? sink : nullptr,
+                                w.sink_part, plan, w.cand, st);
+  else
+    e = pk::launch_search_half(bf16, q, subkeys, T, H, n, S, k, qstats, has_sink ? sink : nullptr,
+                               w.sink_part, w.cand, w.cnts, w.thr, hidx, w.half_score, w.ovf, st);
   if (e != hipSuccess) return hip_status(e, fn);
   if (nex > 0) {
     rc = check_indices(fn, ex_idx, T * H * nex, (int64_t)S * S, st);
     if (rc) return rc;
   }
-  e = pk::launch_cartesian(hidx, w.half_score, T, H, S, k, bf16, q, subkeys, n, ex_idx, nex,
+  e = pk::launch_cartesian(hidx, w.half_score, w.cand, plan, half_idx_out, T, H, S, k, bf16, q, subkeys, n, ex_idx, nex,
                            has_sink ? w.sink_part : nullptr, sink_row0, idx_out, w_out, score_out,
                            st);
   if (e != hipSuccess) return hip_status(e, fn);

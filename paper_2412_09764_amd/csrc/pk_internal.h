@@ -53,6 +53,18 @@ hipError_t launch_search_half(bool bf16, const void* q, const void* subkeys, int
                               float* sink_part, uint64_t* cand, uint32_t* cnts, float* thr,
                               int32_t* half_idx, float* half_score, uint32_t* ovf,
                               hipStream_t st);
+// Few rows: the sub-keys split into `parts` parts of `rows` each, `slices`
+// workgroups per part (search_split.hip).  False: not this call's path.
+constexpr int SPLIT_PARTS_MAX = 16;
+struct SplitPlan {
+  int rows, parts, cap, slices;
+};
+bool split_plan(bool bf16, int64_t T, int H, int S, int k, SplitPlan* plan);
+// Leaves cap record slots per token and part in cand (the candidate runs).
+hipError_t launch_search_split(bool bf16, const void* q, const void* subkeys, int64_t T, int H,
+                               int n, int S, int k, const float2* qstats, const void* sink,
+                               float* sink_part, const SplitPlan& plan, uint64_t* cand,
+                               hipStream_t st);
 // LayerNorm statistics of rows = T*H queries of n elements into stats, and
 // (qhat non-null) the normalised queries in the query dtype.
 hipError_t launch_qnorm(bool bf16, const void* q, int64_t rows, int n, float eps, float2* stats,
@@ -60,8 +72,10 @@ hipError_t launch_qnorm(bool bf16, const void* q, int64_t rows, int n, float eps
 // nex extra key-value pairs per (token, head) (ex_idx [T,H,nex], scored from q
 // and the sub-keys) join the softmax after the k selected; outputs then have
 // k + nex slots per row.  nex = 0: q, subkeys and ex_idx are not read.
-hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, int64_t T, int H,
-                            int S, int k, bool bf16, const void* q, const void* subkeys, int n,
+// parts > 0: the half lists come from the part records of launch_search_split
+// (half_idx and half_score are not read) and go to half_out unless null.
+hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, const uint64_t* recs,
+                            const SplitPlan& plan, int32_t* half_out, int64_t T, int H, int S, int k, bool bf16, const void* q, const void* subkeys, int n,
                             const int64_t* ex_idx, int nex, const float* sink_part,
                             int64_t sink_row0, int64_t* idx_out, float* w_out, float* score_out,
                             hipStream_t st);

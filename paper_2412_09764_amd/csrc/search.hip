@@ -57,6 +57,8 @@
 //     to the query dtype, so the normalised queries never go through memory.
 //   * With a sink (a fixed key per head), the kernel's prologue also forms
 //     each half's part of q . sink[h] from the query fragments in registers.
+// Calls of few rows form the half lists' records in k_score_split instead
+// (search_split.hip), and k_cartesian merges them.
 // Step 2, k_cartesian: per (token, head) the top k of the sums s1[a] + s2[b]
 //   over rank pairs with (a+1)(b+1) <= k (every other pair is beaten by at
 //   least k pairs), ordered (sum desc, composed index i1*S + i2 asc), then the
@@ -64,11 +66,9 @@
 //   caller adds, scored in the same kernel, and the sink's score).
 #include "pk_device.h"
 #include "pk_internal.h"
+#include "pk_mfma.h"
 
 namespace pk {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int CHUNK_ROWS = 64;  // sub-keys per LDS chunk = two MFMA tiles
 #ifndef PK_SCORE_SPLIT8
@@ -76,73 +76,9 @@ constexpr int CHUNK_ROWS = 64;  // sub-keys per LDS chunk = two MFMA tiles
 #endif
 constexpr int SPLIT8 = PK_SCORE_SPLIT8;
 
-// Lambdas of the scoring kernel are always inlined: register arrays indexed
-// by their arguments must see those arguments as constants.
-#define PK_INLINE __attribute__((always_inline))
-
 #ifndef PK_SCORE_PREFETCH
 #define PK_SCORE_PREFETCH 1  // LDS fragments read this many MFMA steps ahead (0: none)
 #endif
-
-template <typename T>
-struct MfmaOp;
-
-template <>
-struct MfmaOp<uint16_t> {  // bf16 storage
-  static constexpr int KSTEP = 16;  // reduction elements per instruction
-  static constexpr int LANE_K = 8;  // reduction elements supplied per lane
-  static constexpr int ESIZE = 2;
-  using frag = bf16x8_t;
-  __device__ static __forceinline__ f32x16_t mma(frag a, frag b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ frag load(const void* p) {
-    return __builtin_bit_cast(frag, *reinterpret_cast<const uint4*>(p));
-  }
-  __device__ static __forceinline__ frag zero() { return __builtin_bit_cast(frag, uint4{0, 0, 0, 0}); }
-  __device__ static __forceinline__ float to_f32(uint16_t v) { return bf16_to_f32(v); }
-  __device__ static __forceinline__ float stored(float v) { return round_bf16_f32(v); }
-  // sum over the fragment's 8 elements of f[i] * s[i] (s: 8 bf16, 16-byte aligned)
-  __device__ static __forceinline__ float dot(frag f, const uint16_t* s) {
-    const uint4 u = __builtin_bit_cast(uint4, f);
-    const uint4 v = *reinterpret_cast<const uint4*>(s);
-    float a = bf16_lo(u.x) * bf16_lo(v.x);
-    a = fmaf(bf16_hi(u.x), bf16_hi(v.x), a);
-    a = fmaf(bf16_lo(u.y), bf16_lo(v.y), a);
-    a = fmaf(bf16_hi(u.y), bf16_hi(v.y), a);
-    a = fmaf(bf16_lo(u.z), bf16_lo(v.z), a);
-    a = fmaf(bf16_hi(u.z), bf16_hi(v.z), a);
-    a = fmaf(bf16_lo(u.w), bf16_lo(v.w), a);
-    return fmaf(bf16_hi(u.w), bf16_hi(v.w), a);
-  }
-  // Normalised fragment, rounded to bf16 (nearest, ties to even).
-  __device__ static __forceinline__ frag normalize(frag f, float mean, float rstd) {
-    uint4 u = __builtin_bit_cast(uint4, f);
-    u.x = pack_bf16x2(qn_apply(bf16_lo(u.x), mean, rstd), qn_apply(bf16_hi(u.x), mean, rstd));
-    u.y = pack_bf16x2(qn_apply(bf16_lo(u.y), mean, rstd), qn_apply(bf16_hi(u.y), mean, rstd));
-    u.z = pack_bf16x2(qn_apply(bf16_lo(u.z), mean, rstd), qn_apply(bf16_hi(u.z), mean, rstd));
-    u.w = pack_bf16x2(qn_apply(bf16_lo(u.w), mean, rstd), qn_apply(bf16_hi(u.w), mean, rstd));
-    return __builtin_bit_cast(frag, u);
-  }
-};
-
-template <>
-struct MfmaOp<float> {
-  static constexpr int KSTEP = 2;
-  static constexpr int LANE_K = 1;
-  static constexpr int ESIZE = 4;
-  using frag = float;
-  __device__ static __forceinline__ f32x16_t mma(frag a, frag b, f32x16_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static __forceinline__ frag load(const void* p) { return *reinterpret_cast<const float*>(p); }
-  __device__ static __forceinline__ frag zero() { return 0.f; }
-  __device__ static __forceinline__ float to_f32(float v) { return v; }
-  __device__ static __forceinline__ float stored(float v) { return v; }
-  __device__ static __forceinline__ frag normalize(frag f, float mean, float rstd) {
-    return qn_apply(f, mean, rstd);
-  }
-};
 
 // Per (token, head) query of n elements (n * esize <= 1 KiB): mean and
 // rstd = 1 / sqrt(var + eps) of LayerNorm without affine (biased variance,
@@ -206,10 +142,6 @@ __global__ __launch_bounds__(256) void k_qnorm(const T* __restrict__ q, int64_t 
     }
   }
 }
-
-// Row of the 32x32 MFMA result held in accumulator slot j of a lane whose
-// upper-half bit is kh (columns are lane & 31).
-__device__ __forceinline__ int acc_row(int j, int kh) { return 8 * (j >> 2) + 4 * kh + (j & 3); }
 
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
@@ -362,8 +294,8 @@ __device__ __forceinline__ uint32_t mask16(const f32x16_t& acc, float b) {
 
 // KBIG (k > 32): the threshold comes from all rows (P = all chunks: no second
 // sweep).
-template <typename T, int NSTEP, bool KBIG>
-__global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
+template <typename T, int NSTEP, bool KBIG, int W>
+__global__ __launch_bounds__(64 * W, 4) void k_score_topk(
     const T* __restrict__ q, const T* __restrict__ subkeys, int64_t ntok, int H, int n, int S,
     int k, const float2* __restrict__ qstats, const T* __restrict__ sink,
     float* __restrict__ sink_part, uint64_t* __restrict__ cand, uint32_t* __restrict__ cnts,
@@ -376,7 +308,7 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   constexpr int RBP = NSLOT * 16;             // row pitch in LDS
   constexpr int EPS = 16 / M::ESIZE;          // elements per segment
   constexpr int CBYTES = CHUNK_ROWS * RBP;
-  constexpr int NDMA = (NSLOT + SEARCH_WAVES - 1) / SEARCH_WAVES;  // loads per wave and chunk, at most
+  constexpr int NDMA = (NSLOT + W - 1) / W;  // loads per wave and chunk, at most
 
   // Sub-key chunks of 64 rows, double buffered, each row followed by a spare
   // 16-byte slot: with a pitch of an odd number of 16-byte slots, the 16
@@ -394,8 +326,8 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   constexpr int XS_WAVE = WAVE * 16 * 4;
   __shared__ __align__(1024) unsigned char kbuf0[CBYTES];
   __shared__ __align__(1024) unsigned char kbuf1[CBYTES];
-  __shared__ __align__(16) unsigned char xsmem[SEARCH_WAVES * XS_WAVE];
-  __shared__ uint32_t dtab[NDMA * SEARCH_WAVES * WAVE];
+  __shared__ __align__(16) unsigned char xsmem[W * XS_WAVE];
+  __shared__ uint32_t dtab[NDMA * W * WAVE];
 
   const int d = n >> 1;
   const int HP = 2 * H;
@@ -405,7 +337,7 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kh = lane >> 5;
   const int col = lane & 31;
-  const int64_t tok = tile * SEARCH_TOK + wave * 32 + col;
+  const int64_t tok = tile * (32 * W) + wave * 32 + col;
   const bool tok_ok = tok < ntok;
   const T* kbase = subkeys + (size_t)hp * S * d;
 
@@ -470,11 +402,11 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   // arithmetic.
 #pragma unroll
   for (int j = 0; j < NDMA; ++j) {
-    const int i = wave + j * SEARCH_WAVES;
+    const int i = wave + j * W;
     if (i < NSLOT) {
       int r;
       const int eb = slot_src(i * WAVE + lane, r);
-      dtab[j * SEARCH_WAVES * WAVE + tid] = (uint32_t)(r * d * M::ESIZE + eb);
+      dtab[j * W * WAVE + tid] = (uint32_t)(r * d * M::ESIZE + eb);
     }
   }
   const int nfull_rows = S / CHUNK_ROWS;  // chunks whose 64 rows all exist
@@ -483,13 +415,13 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
       const uint32_t cb = (uint32_t)((size_t)c * CHUNK_ROWS * d * M::ESIZE);
 #pragma unroll
       for (int j = 0; j < NDMA; ++j) {
-        const int i = wave + j * SEARCH_WAVES;
-        if (NSLOT % SEARCH_WAVES == 0 || i < NSLOT)
-          lds_dma16_buf(ktab, dtab[j * SEARCH_WAVES * WAVE + tid], cb, &buf[i * WAVE * 16]);
+        const int i = wave + j * W;
+        if (NSLOT % W == 0 || i < NSLOT)
+          lds_dma16_buf(ktab, dtab[j * W * WAVE + tid], cb, &buf[i * WAVE * 16]);
       }
       return;
     }
-    for (int i = wave; i < NSLOT; i += SEARCH_WAVES) {
+    for (int i = wave; i < NSLOT; i += W) {
       int r;
       const int eb = slot_src(i * WAVE + lane, r);
       int row = c * CHUNK_ROWS + r;
@@ -607,7 +539,7 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   // sweeps, when the chunk buffers are free.
   auto kth_of_maxima = [&]() PK_INLINE -> float {
     sort_desc_f16x32(mxp);
-    uint16_t* const runs = reinterpret_cast<uint16_t*>(xsmem);  // [64 * SEARCH_WAVES][32]
+    uint16_t* const runs = reinterpret_cast<uint16_t*>(xsmem);  // [64 * W][32]
     uint4* const mine = reinterpret_cast<uint4*>(runs + tid * 32);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -662,7 +594,7 @@ __global__ __launch_bounds__(64 * SEARCH_WAVES, 4) void k_score_topk(
   const size_t rid = ((size_t)(tok_ok ? tok : 0) * H + h) * 2 + p;
   // this wave's run (the wave index taken as uniform, so the run's buffer
   // resource lives in scalar registers as the store instruction needs)
-  const size_t wr = (((size_t)tile * SEARCH_WAVES + __builtin_amdgcn_readfirstlane(wave)) * H + h) * 2 + p;
+  const size_t wr = (((size_t)tile * W + __builtin_amdgcn_readfirstlane(wave)) * H + h) * 2 + p;
   uint32_t taken = 0;   // records of this lane since the last restart
   uint32_t wcnt = 0;    // records of the wave (uniform)
   float bound = INFINITY;
@@ -947,6 +879,114 @@ __global__ __launch_bounds__(256) void k_topk_fallback(const T* __restrict__ q,
   }
 }
 
+// The rank pairs (a, b) with (a + 1) * (b + 1) <= PKMEM_KMAX, by that product:
+// the pairs that can reach the top k of the sums are the first
+// cartesian_pairs(k) of them, for every k.
+constexpr int PAIRS_MAX = 280;
+struct PairTable {
+  uint16_t v[PAIRS_MAX];
+};
+constexpr PairTable make_pairs() {
+  PairTable t{};
+  int m = 0;
+  for (int prod = 1; prod <= 64; ++prod)
+    for (int a = 1; a <= prod; ++a)
+      if (prod % a == 0) t.v[m++] = (uint16_t)(((a - 1) << 8) | (prod / a - 1));
+  return t;
+}
+__device__ constexpr PairTable PAIRS = make_pairs();
+
+// The sorted top k (lane j: rank j) of each half's nrec part records (empty
+// slots 0), at most EM of them per lane.  As in the parts
+// themselves, the k-th largest of the 64 lane maxima bounds the selection;
+// the records at or above it (about 44 at k = 32, however many there are) meet
+// in one sort of 64.  More than 64 of them (k from about 40, ties) are cut by a
+// bit search over the (distinct) keys, score bits first.  The two halves go side by side.
+template <int EM>
+__device__ __forceinline__ void merge_parts(const uint64_t* const (&rec)[2], int nrec, int k,
+                                            int lane, uint64_t (*stage)[WAVE], uint64_t (&out)[2]) {
+  if constexpr (EM == 1) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) out[p] = lane < nrec ? rec[p][lane] : 0ull;
+  } else {
+    uint64_t v[2][EM];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int e = 0; e < EM; ++e) v[p][e] = e * WAVE + lane < nrec ? rec[p][e * WAVE + lane] : 0ull;
+    uint32_t u[2], thr[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      u[p] = 0;
+#pragma unroll
+      for (int e = 0; e < EM; ++e) {
+        const uint32_t hi = (uint32_t)(v[p][e] >> 32);
+        u[p] = hi > u[p] ? hi : u[p];
+      }
+      thr[p] = 0;
+    }
+#pragma unroll
+    for (int b = 31; b >= 16; --b)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const uint32_t c = thr[p] | (1u << b);
+        if (__popcll(__builtin_amdgcn_ballot_w64(u[p] >= c)) >= k) thr[p] = c;
+      }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      uint64_t low = (uint64_t)(thr[p] ? thr[p] : 1u) << 32;  // an empty slot is below it
+      uint32_t cnt = 0;
+#pragma unroll
+      for (int e = 0; e < EM; ++e)
+        cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(v[p][e] >= low));
+      if (cnt > (uint32_t)WAVE) {
+        uint32_t x = 0;  // the k-th largest score
+        for (int b = 31; b >= 0; --b) {
+          const uint32_t c = x | (1u << b);
+          uint32_t have = 0;
+#pragma unroll
+          for (int e = 0; e < EM; ++e)
+            have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64((uint32_t)(v[p][e] >> 32) >= c));
+          if (have >= (uint32_t)k) x = c;
+        }
+        low = (uint64_t)x << 32;
+        cnt = 0;
+#pragma unroll
+        for (int e = 0; e < EM; ++e)
+          cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(v[p][e] >= low));
+        // ties at it: the lowest rows (the low words are complements)
+        for (int b = 31; b >= 0 && cnt > (uint32_t)WAVE; --b) {
+          const uint64_t c = low | (1ull << b);
+          uint32_t have = 0;
+#pragma unroll
+          for (int e = 0; e < EM; ++e)
+            have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(v[p][e] >= c));
+          if (have >= (uint32_t)k) {
+            low = c;
+            cnt = have;
+          }
+        }
+      }
+      cnt = 0;
+#pragma unroll
+      for (int e = 0; e < EM; ++e) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(v[p][e] >= low);
+        const uint32_t at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (v[p][e] >= low) stage[p][at] = v[p][e];
+        cnt += (uint32_t)__popcll(m);
+      }
+      out[p] = (uint32_t)lane < cnt ? stage[p][lane] : 0ull;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    uint64_t s[1] = {out[p]};
+    wave_sort_desc<1>(s, lane);
+    out[p] = s[0];
+  }
+}
+
 // Extra key-value pairs (EXTRA): the row's nex caller-given composed indices
 // are scored like any full key, q1 . K1[i1] + q2 . K2[i2] (lane l holds
 // elements 4l..4l+3 of each half, fp32 products summed over the wave), and
@@ -958,9 +998,13 @@ __global__ __launch_bounds__(256) void k_topk_fallback(const T* __restrict__ q,
 // sink_row0 + h.
 // MODE: 0 = the k selected only, 1 = extra pairs (and the sink, if given),
 // 2 = the sink only.
-template <int E, typename T, int MODE>
+// EM > 0: no half lists yet; the row's part records (k_score_split) are merged
+// here, at most EM per lane, and the half lists written to half_out when non-null.
+template <int E, typename T, int MODE, int EM>
 __global__ __launch_bounds__(256) void k_cartesian(const int32_t* __restrict__ half_idx,
                                                    const float* __restrict__ half_score,
+                                                   const uint64_t* __restrict__ recs, int nrec,
+                                                   int32_t* __restrict__ half_out,
                                                    int64_t rows, int S, int k, int npairs,
                                                    const T* __restrict__ q,
                                                    const T* __restrict__ subkeys, int H, int n,
@@ -970,18 +1014,18 @@ __global__ __launch_bounds__(256) void k_cartesian(const int32_t* __restrict__ h
                                                    int64_t* __restrict__ idx_out,
                                                    float* __restrict__ w_out,
                                                    float* __restrict__ score_out) {
-  __shared__ uint32_t pairs[WAVE * E];
-  if (threadIdx.x == 0) {
-    int m = 0;
-    for (int a = 0; a < k; ++a)
-      for (int b = 0; b < k / (a + 1); ++b) pairs[m++] = (uint32_t(a) << 16) | uint32_t(b);
-  }
-  __syncthreads();
+  __shared__ uint64_t stage[EM > 1 ? 4 : 1][2][WAVE];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t pair[E];  // this lane's rank pairs
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int m = e * WAVE + lane;
+    pair[e] = PAIRS.v[m < npairs ? m : 0];
+  }
   constexpr bool EXTRA = MODE != 0;
   const int nsc = EXTRA ? nex + (sink_part ? 1 : 0) : 0;  // full keys scored per row
   const int kk = k + nsc;                             // slots per row
-  if constexpr (!EXTRA) {
+  if constexpr (!EXTRA && EM == 0) {
     // Two rows per pass (this wave's next grid-stride row beside it): their
     // loads, their candidate keys and their two sorts run side by side.
     auto build = [&](int64_t row, uint64_t (&v)[E]) PK_INLINE {
@@ -994,8 +1038,7 @@ __global__ __launch_bounds__(256) void k_cartesian(const int32_t* __restrict__ h
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int m = e * WAVE + lane;
-        const uint32_t pr = pairs[m < npairs ? m : 0];
-        const int a = (int)(pr >> 16), b = (int)(pr & 0xFFFFu);
+        const int a = (int)(pair[e] >> 8), b = (int)(pair[e] & 0xFFu);
         const float sa = __shfl(s1v, a, WAVE), sb = __shfl(s2v, b, WAVE);
         const int ia = __shfl(i1v, a, WAVE), ib = __shfl(i2v, b, WAVE);
         v[e] = m < npairs ? make_key(sa + sb, (uint32_t)ia * (uint32_t)S + (uint32_t)ib) : 0ull;
@@ -1104,20 +1147,39 @@ __global__ __launch_bounds__(256) void k_cartesian(const int32_t* __restrict__ h
       }
       if (sink_part && lane == nex) ex_score = sink_part[(size_t)row * 2] + sink_part[(size_t)row * 2 + 1];
     }
-    const int32_t* i1 = half_idx + (size_t)row * 2 * k;
-    const int32_t* i2 = i1 + k;
-    const float* s1 = half_score + (size_t)row * 2 * k;
-    const float* s2 = s1 + k;
-    const float s1v = lane < k ? s1[lane] : 0.f;
-    const float s2v = lane < k ? s2[lane] : 0.f;
-    const int i1v = lane < k ? i1[lane] : 0;
-    const int i2v = lane < k ? i2[lane] : 0;
+    float s1v, s2v;
+    int i1v, i2v;
+    if constexpr (EM > 0) {
+      const int64_t t = row / H;
+      const uint64_t* const rp =
+          recs + ((size_t)(t >> 5) * H + (size_t)(row - t * H)) * 2 * (32 * CAND_CAP) +
+          (size_t)(t & 31) * nrec;
+      const uint64_t* const rec[2] = {rp, rp + 32 * CAND_CAP};
+      uint64_t top[2];
+      merge_parts<EM>(rec, nrec, k, lane, stage[EM > 1 ? wave : 0], top);
+      s1v = lane < k ? key_score(top[0]) : 0.f;
+      s2v = lane < k ? key_score(top[1]) : 0.f;
+      i1v = lane < k ? (int)key_index(top[0]) : 0;
+      i2v = lane < k ? (int)key_index(top[1]) : 0;
+      if (half_out && lane < k) {
+        half_out[(size_t)row * 2 * k + lane] = i1v;
+        half_out[(size_t)row * 2 * k + k + lane] = i2v;
+      }
+    } else {
+      const int32_t* i1 = half_idx + (size_t)row * 2 * k;
+      const int32_t* i2 = i1 + k;
+      const float* s1 = half_score + (size_t)row * 2 * k;
+      const float* s2 = s1 + k;
+      s1v = lane < k ? s1[lane] : 0.f;
+      s2v = lane < k ? s2[lane] : 0.f;
+      i1v = lane < k ? i1[lane] : 0;
+      i2v = lane < k ? i2[lane] : 0;
+    }
     uint64_t v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int m = e * WAVE + lane;
-      const uint32_t pr = pairs[m < npairs ? m : 0];
-      const int a = (int)(pr >> 16), b = (int)(pr & 0xFFFFu);
+      const int a = (int)(pair[e] >> 8), b = (int)(pair[e] & 0xFFu);
       const float sa = __shfl(s1v, a, WAVE), sb = __shfl(s2v, b, WAVE);
       const int ia = __shfl(i1v, a, WAVE), ib = __shfl(i2v, b, WAVE);
       v[e] = m < npairs ? make_key(sa + sb, (uint32_t)ia * (uint32_t)S + (uint32_t)ib) : 0ull;
@@ -1156,24 +1218,31 @@ int cartesian_pairs(int k) {
   return m;
 }
 
+template <typename T, int NSTEP, int W>
+static void launch_score_waves(const void* q, const void* subkeys, int64_t T_, int H, int n, int S,
+                               int k, const float2* qstats, const void* sink, float* sink_part,
+                               uint64_t* cand, uint32_t* cnts, float* thr, hipStream_t st) {
+  const dim3 g((unsigned)((T_ + 32 * W - 1) / (32 * W) * 2 * H)), b(64 * W);
+  if (k > 32)
+    hipLaunchKernelGGL((k_score_topk<T, NSTEP, true, W>), g, b, 0, st, (const T*)q,
+                       (const T*)subkeys, T_, H, n, S, k, qstats, (const T*)sink, sink_part, cand,
+                       cnts, thr);
+  else
+    hipLaunchKernelGGL((k_score_topk<T, NSTEP, false, W>), g, b, 0, st, (const T*)q,
+                       (const T*)subkeys, T_, H, n, S, k, qstats, (const T*)sink, sink_part, cand,
+                       cnts, thr);
+}
+
 template <typename T, int NSTEP>
 static hipError_t launch_score(const void* q, const void* subkeys, int64_t T_, int H, int n, int S,
                                int k, const float2* qstats, const void* sink, float* sink_part,
                                uint64_t* cand, uint32_t* cnts, float* thr,
                                int32_t* half_idx, float* half_score, uint32_t* ovf,
                                hipStream_t st) {
-  const int64_t tiles = (T_ + SEARCH_TOK - 1) / SEARCH_TOK;
-  const int64_t blocks = tiles * 2 * H;
   {
     LaunchTimer lt("score_topk", st);
-    if (k > 32)
-      hipLaunchKernelGGL((k_score_topk<T, NSTEP, true>), dim3((unsigned)blocks), dim3(64 * SEARCH_WAVES),
-                         0, st, (const T*)q, (const T*)subkeys, T_, H, n, S, k, qstats,
-                         (const T*)sink, sink_part, cand, cnts, thr);
-    else
-      hipLaunchKernelGGL((k_score_topk<T, NSTEP, false>), dim3((unsigned)blocks), dim3(64 * SEARCH_WAVES),
-                         0, st, (const T*)q, (const T*)subkeys, T_, H, n, S, k, qstats,
-                         (const T*)sink, sink_part, cand, cnts, thr);
+    launch_score_waves<T, NSTEP, SEARCH_WAVES>(q, subkeys, T_, H, n, S, k, qstats, sink, sink_part,
+                                               cand, cnts, thr, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1230,48 +1299,64 @@ hipError_t launch_search_half(bool bf16, const void* q, const void* subkeys, int
   return launch_score<float, 32>(q, subkeys, T_, H, n, S, k, qstats, sink, sink_part, cand, cnts, thr, half_idx, half_score, ovf, st);
 }
 
-template <int E>
-static void cart_launch(dim3 g, dim3 b, hipStream_t st, const int32_t* half_idx,
-                        const float* half_score, int64_t rows, int S, int k, int np, bool bf16,
-                        const void* q, const void* subkeys, int H, int n, const int64_t* ex_idx,
-                        int nex, const float* sink_part, int64_t sink_row0, int64_t* idx_out,
-                        float* w_out, float* score_out) {
+// The part records k_cartesian merges itself (nrec > 0), or the half lists.
+struct CartIn {
+  const int32_t* half_idx;
+  const float* half_score;
+  const uint64_t* recs;
+  int nrec;  // per token
+  int32_t* half_out;
+};
+
+template <int E, int EM>
+static void cart_launch(dim3 g, dim3 b, hipStream_t st, const CartIn& in, int64_t rows, int S, int k,
+                        int np, bool bf16, const void* q, const void* subkeys, int H, int n,
+                        const int64_t* ex_idx, int nex, const float* sink_part, int64_t sink_row0,
+                        int64_t* idx_out, float* w_out, float* score_out) {
+#define PK_CART(TY, MODE, Q, K, EX, NEX, SINK, ROW0)                                             \
+  hipLaunchKernelGGL((k_cartesian<E, TY, MODE, EM>), g, b, 0, st, in.half_idx, in.half_score,      \
+                     in.recs, in.nrec, in.half_out, rows, S, k, np, (const TY*)(Q),              \
+                     (const TY*)(K), H, n, EX, NEX, SINK, ROW0, idx_out, w_out, score_out)
   if (nex == 0 && !sink_part)
-    hipLaunchKernelGGL((k_cartesian<E, uint16_t, 0>), g, b, 0, st, half_idx, half_score, rows,
-                       S, k, np, (const uint16_t*)nullptr, (const uint16_t*)nullptr, H, n,
-                       (const int64_t*)nullptr, 0, (const float*)nullptr, (int64_t)0, idx_out,
-                       w_out, score_out);
+    PK_CART(uint16_t, 0, nullptr, nullptr, (const int64_t*)nullptr, 0, (const float*)nullptr, (int64_t)0);
   else if (nex == 0)
-    hipLaunchKernelGGL((k_cartesian<E, uint16_t, 2>), g, b, 0, st, half_idx, half_score, rows,
-                       S, k, np, (const uint16_t*)nullptr, (const uint16_t*)nullptr, H, n,
-                       (const int64_t*)nullptr, 0, sink_part, sink_row0, idx_out, w_out,
-                       score_out);
+    PK_CART(uint16_t, 2, nullptr, nullptr, (const int64_t*)nullptr, 0, sink_part, sink_row0);
   else if (bf16)
-    hipLaunchKernelGGL((k_cartesian<E, uint16_t, 1>), g, b, 0, st, half_idx, half_score, rows, S,
-                       k, np, (const uint16_t*)q, (const uint16_t*)subkeys, H, n, ex_idx, nex,
-                       sink_part, sink_row0, idx_out, w_out, score_out);
+    PK_CART(uint16_t, 1, q, subkeys, ex_idx, nex, sink_part, sink_row0);
   else
-    hipLaunchKernelGGL((k_cartesian<E, float, 1>), g, b, 0, st, half_idx, half_score, rows, S, k,
-                       np, (const float*)q, (const float*)subkeys, H, n, ex_idx, nex,
-                       sink_part, sink_row0, idx_out, w_out, score_out);
+    PK_CART(float, 1, q, subkeys, ex_idx, nex, sink_part, sink_row0);
+#undef PK_CART
 }
 
-hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, int64_t T_, int H,
-                            int S, int k, bool bf16, const void* q, const void* subkeys, int n,
-                            const int64_t* ex_idx, int nex, const float* sink_part,
-                            int64_t sink_row0, int64_t* idx_out, float* w_out, float* score_out,
-                            hipStream_t st) {
+hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, const uint64_t* recs,
+                            const SplitPlan& plan, int32_t* half_out, int64_t T_, int H, int S, int k, bool bf16,
+                            const void* q, const void* subkeys, int n, const int64_t* ex_idx,
+                            int nex, const float* sink_part, int64_t sink_row0, int64_t* idx_out,
+                            float* w_out, float* score_out, hipStream_t st) {
   const int64_t rows = T_ * H;
   const int np = cartesian_pairs(k);
   int64_t blocks = (rows + 3) / 4;
   if (blocks > 8192) blocks = 8192;
   if (blocks < 1) blocks = 1;
   const dim3 g((unsigned)blocks), b(256);
+  const int nrec = plan.parts * plan.cap;
+  const CartIn in{half_idx, half_score, recs, nrec, half_out};
   LaunchTimer lt("cartesian", st);
-  if (np <= 64) cart_launch<1>(g, b, st, half_idx, half_score, rows, S, k, np, bf16, q, subkeys, H, n, ex_idx, nex, sink_part, sink_row0, idx_out, w_out, score_out);
-  else if (np <= 128) cart_launch<2>(g, b, st, half_idx, half_score, rows, S, k, np, bf16, q, subkeys, H, n, ex_idx, nex, sink_part, sink_row0, idx_out, w_out, score_out);
-  else if (np <= 256) cart_launch<4>(g, b, st, half_idx, half_score, rows, S, k, np, bf16, q, subkeys, H, n, ex_idx, nex, sink_part, sink_row0, idx_out, w_out, score_out);
-  else cart_launch<8>(g, b, st, half_idx, half_score, rows, S, k, np, bf16, q, subkeys, H, n, ex_idx, nex, sink_part, sink_row0, idx_out, w_out, score_out);
+#define PK_CART_EM(E, EM)                                                                          \
+  cart_launch<E, EM>(g, b, st, in, rows, S, k, np, bf16, q, subkeys, H, n, ex_idx, nex, sink_part, \
+                     sink_row0, idx_out, w_out, score_out)
+#define PK_CART_E(E)                        \
+  if (nrec == 0) PK_CART_EM(E, 0);          \
+  else if (nrec <= 64) PK_CART_EM(E, 1);    \
+  else if (nrec <= 256) PK_CART_EM(E, 4);   \
+  else if (nrec <= 512) PK_CART_EM(E, 8);   \
+  else PK_CART_EM(E, SPLIT_PARTS_MAX)
+  if (np <= 64) { PK_CART_E(1); }
+  else if (np <= 128) { PK_CART_E(2); }
+  else if (np <= 256) { PK_CART_E(4); }
+  else { PK_CART_E(8); }
+#undef PK_CART_E
+#undef PK_CART_EM
   return hipGetLastError();
 }
 
