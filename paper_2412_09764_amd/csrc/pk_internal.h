@@ -26,13 +26,6 @@ class LaunchTimer {
 // the per-row sort of the search; the 32 rows of a scoring wave share one run
 // of 32 * CAND_CAP records.
 constexpr int CAND_CAP = 256;
-// Waves and tokens per workgroup of the scoring kernel (32 tokens per wave).
-#ifndef PK_SEARCH_WAVES
-#define PK_SEARCH_WAVES 16
-#endif
-constexpr int SEARCH_WAVES = PK_SEARCH_WAVES;
-constexpr int SEARCH_TOK = 32 * SEARCH_WAVES;
-
 // Number of (i1, i2) rank pairs with (i1 + 1) * (i2 + 1) <= k: only these can
 // reach the top k of the k*k sums when both half lists are sorted.
 int cartesian_pairs(int k);

@@ -3,8 +3,9 @@
 //
 // Step 1, k_score_topk: for every (token, head, half) row, the top k of the S
 // half-key scores s[i] = q_half . K_half[i], ordered (score desc, index asc).
-//   * A workgroup owns SEARCH_TOK = 512 tokens (16 waves of 32, four per SIMD)
-//     of one (head, half); the (head, half) index is blockIdx % (2H), so with
+//   * A workgroup owns 512 tokens (16 waves of 32, four per SIMD; 4 or 8 waves
+//     where that still leaves no more workgroups than CUs) of one (head,
+//     half); the (head, half) index is blockIdx % (2H), so with
 //     2H = 8 each XCD streams only its own sub-key table and keeps it in its
 //     L2.  The kernel fits 128 registers, which is what four waves per SIMD
 //     allow.
@@ -1241,8 +1242,19 @@ static hipError_t launch_score(const void* q, const void* subkeys, int64_t T_, i
                                hipStream_t st) {
   {
     LaunchTimer lt("score_topk", st);
-    launch_score_waves<T, NSTEP, SEARCH_WAVES>(q, subkeys, T_, H, n, S, k, qstats, sink, sink_part,
-                                               cand, cnts, thr, st);
+    auto wgs = [&](int w) { return (T_ + 32 * w - 1) / (32 * w) * 2 * H; };
+    // The smallest workgroup that keeps the call within one workgroup per CU:
+    // 16 waves share each sub-key chunk best (16000 tokens, S = 2048: 174 us
+    // against 200 with 8, 303 with 4) but leave CUs idle below 512 tokens x
+    // 256 (4000 tokens: 80 us with 4, 98 with 8, 141 with 16; 8000 tokens at
+    // S = 8192: 316 with 8, 430 with 16, 475 with 4).
+    const int W = wgs(4) <= 256 ? 4 : wgs(8) <= 256 ? 8 : 16;
+#define PK_WAVES(W) \
+  launch_score_waves<T, NSTEP, W>(q, subkeys, T_, H, n, S, k, qstats, sink, sink_part, cand, cnts, thr, st)
+    if (W == 4) PK_WAVES(4);
+    else if (W == 8) PK_WAVES(8);
+    else PK_WAVES(16);
+#undef PK_WAVES
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
