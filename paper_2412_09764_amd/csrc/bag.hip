@@ -73,6 +73,24 @@ struct LookupChunk {
   }
 };
 
+// Two adjacent elements of a value-dtype row, rounded once.
+__device__ __forceinline__ void store_pair(uint16_t* p, float a, float b) {
+  *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(a, b);
+}
+__device__ __forceinline__ void store_pair(float* p, float a, float b) {
+  *reinterpret_cast<float2*>(p) = make_float2(a, b);
+}
+__device__ __forceinline__ void load_pair(const uint16_t* p, float& a, float& b) {
+  const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
+  a = bf16_lo(u);
+  b = bf16_hi(u);
+}
+__device__ __forceinline__ void load_pair(const float* p, float& a, float& b) {
+  const float2 u = *reinterpret_cast<const float2*>(p);
+  a = u.x;
+  b = u.y;
+}
+
 // y[t] = sum_j w[t,j] V[idx[t,j]]; fp32 accumulation, one rounding at the end.
 // The output rows are stored non-temporal: a trickle of ordinary stores in the
 // middle of the gather's random-read stream costs it about 12% on MI355X.
@@ -214,6 +232,92 @@ __global__ __launch_bounds__(256) void k_bag_fwd(const V* __restrict__ values, i
         if (ok[i]) st16_nt(y + t * D + (size_t)(i * CL + cl) * R::N, R::pack(acc[i]));
     }
   }
+  }
+}
+
+// The bag of few tokens: a workgroup of W waves per (token, 1 KiB slab of the
+// row), wave w taking the w-th contiguous part of the token's lookups, eight
+// lookups' loads in flight per lane group; the waves' fp32 sums meet in LDS and
+// are added in wave order (the same bits on every run), two elements per
+// thread.  With one wave per token a few tokens are bound by the latency of
+// one wave's loads (128 lookups of 4 KiB: 42 us for 32 tokens, 7.4 us here).
+template <typename V, int CL, int W>
+__global__ __launch_bounds__(64 * W) void k_bag_fwd_split(
+    const V* __restrict__ values, int D, const int64_t* __restrict__ idx,
+    const float* __restrict__ w, int bag, int nslab, V* __restrict__ y,
+    const V* __restrict__ gate, V* __restrict__ y_plain) {
+  using R = Row16<V>;
+  constexpr int G = WAVE / CL;
+  constexpr int U = 8;
+  constexpr int SE = CL * R::N;  // elements of a slab
+  __shared__ __align__(16) float part[W][SE];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = blockIdx.x / nslab;
+  const int slab = (int)(blockIdx.x % nslab);
+  const int grp = lane / CL, cl = lane % CL;
+  const int e0 = (slab * CL + cl) * R::N;
+  const bool ok = e0 < D;
+  const int per = (bag + W - 1) / W;
+  const int j0 = wave * per, j1 = j0 + per < bag ? j0 + per : bag;
+  const V* col = values + (ok ? e0 : 0);
+  float acc[R::N];
+#pragma unroll
+  for (int e = 0; e < R::N; ++e) acc[e] = 0.f;
+  for (int c0 = j0; c0 < j1; c0 += WAVE) {
+    const int nb = j1 - c0 < WAVE ? j1 - c0 : WAVE;
+    LookupChunk<G> lk;
+    lk.load(idx + t * bag, w + t * bag, c0, nb, lane);
+    for (int b = 0; b < nb; b += U * G) {
+      uint4 v[U];
+      float ww[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = b + u * G + grp;
+        int64_t r;
+        lk.get(G == 1 ? (j < nb ? j : b) : (j < nb ? j : 0), r, ww[u]);
+        const bool live = j < nb && ok;
+        v[u] = live ? ld16_nt(col + r * D) : uint4{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (b + u * G >= nb) break;  // the same for the whole wave
+        float f[R::N];
+        R::unpack(v[u], f);
+#pragma unroll
+        for (int e = 0; e < R::N; ++e) acc[e] = fmaf(ww[u], f[e], acc[e]);
+      }
+    }
+  }
+  if (G > 1) {
+#pragma unroll
+    for (int m = CL; m < WAVE; m <<= 1)
+#pragma unroll
+      for (int e = 0; e < R::N; ++e) acc[e] += __shfl_xor(acc[e], m, WAVE);
+  }
+  if (grp == 0) {
+#pragma unroll
+    for (int e = 0; e < R::N; ++e) part[wave][cl * R::N + e] = acc[e];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x * 2; i < SE; i += 128 * W) {
+    const int e = slab * SE + i;
+    if (e >= D) break;
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+      const float2 pv = *reinterpret_cast<const float2*>(&part[x][i]);
+      a += pv.x;
+      b += pv.y;
+    }
+    const size_t off = (size_t)t * D + e;
+    if (gate) {
+      if (y_plain) store_pair(y_plain + off, a, b);
+      float ga, gb;
+      load_pair(gate + off, ga, gb);
+      a *= silu_f32(ga);
+      b *= silu_f32(gb);
+    }
+    store_pair(y + off, a, b);
   }
 }
 
@@ -404,6 +508,37 @@ hipError_t launch_bag_forward(bool bf16, const void* values, int D, const int64_
   if (T <= 0) return hipSuccess;
   const int C = D * (bf16 ? 2 : 4) / 16;
   LaunchTimer lt("bag_forward", st);
+  // Few tokens: the bag split over waves while the call has at most 2048
+  // slabs (one wave per token against the split: D = 2048, 32 tokens 42 / 7.4
+  // us, 512 55 / 48, 1024 89 / 91; D = 256, 1024 tokens 19 / 14, 2000 24 / 24)
+  // and each wave's lane groups have lookups enough to be worth it (bag 8 at
+  // D = 64 fp32: 2.9 / 3.4).  Narrow rows take 4 waves (D = 64, 512 tokens:
+  // 5.0 against 5.6 with 8), others 8 (D = 2048, 1 token: 5.0 against 6.6).
+  const int nslab = (C + 63) / 64;
+  if (T * nslab <= 2048 && (int64_t)bag * (C < 64 ? C : 64) >= 8 * WAVE) {
+    const dim3 grid((unsigned)(T * nslab));
+#define PK_SPLIT(CL)                                                                               \
+  do {                                                                                             \
+    constexpr int W = (CL) < 32 ? 4 : 8;                                                           \
+    if (bf16)                                                                                      \
+      hipLaunchKernelGGL((k_bag_fwd_split<uint16_t, CL, W>), grid, dim3(64 * W), 0, st,            \
+                         (const uint16_t*)values, D, idx, w, bag, nslab, (uint16_t*)y,             \
+                         (const uint16_t*)gate, (uint16_t*)y_plain);                               \
+    else                                                                                           \
+      hipLaunchKernelGGL((k_bag_fwd_split<float, CL, W>), grid, dim3(64 * W), 0, st,               \
+                         (const float*)values, D, idx, w, bag, nslab, (float*)y,                   \
+                         (const float*)gate, (float*)y_plain);                                     \
+  } while (0)
+    if (C > 32) PK_SPLIT(64);
+    else if (C > 16) PK_SPLIT(32);
+    else if (C > 8) PK_SPLIT(16);
+    else if (C > 4) PK_SPLIT(8);
+    else if (C > 2) PK_SPLIT(4);
+    else if (C > 1) PK_SPLIT(2);
+    else PK_SPLIT(1);
+#undef PK_SPLIT
+    return hipGetLastError();
+  }
   // Full rows of 4 or 8 slabs are split over PK_FWD_SPLIT waves per token.
   constexpr int SP = PK_FWD_SPLIT;
   if (C == 256 && (4 % SP) == 0) {
