@@ -75,10 +75,19 @@ hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, co
 
 // ---- search backward (search_bwd.hip) --------------------------------------
 size_t search_backward_ws_bytes(int64_t T, int H, int k);
+// Items to sort: keys (int64 or u32, by the call), or with counts rows of k
+// u32 slots of which row r fills its first counts[r].
+struct SortSrc {
+  const void* keys;
+  const uint32_t* counts;
+  int k;
+};
+constexpr int64_t SORT_SLOTS_MAX = (int64_t)1 << 19;  // slots a sort takes as they are
 void sort_u32_inputs(void* ws, int64_t Lmax, uint32_t** keys_in, uint32_t** vals_in);
-hipError_t sort_u32_segments(int64_t Lmax, const uint32_t* Ldev, int key_bits, void* ws,
-                             const uint32_t** ks, const uint32_t** vs, const uint32_t** seg,
-                             const uint32_t** nseg, hipStream_t st);
+hipError_t sort_u32_segments(const SortSrc* slots, int64_t Lmax, const uint32_t* Ldev, int key_bits,
+                             void* ws, uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
+                             const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
+                             const uint32_t** nlong, hipStream_t st);
 size_t scan_scratch_u32(int64_t n);
 hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStream_t st);
 // qstats (nullable): the queries were normalised in the forward (their
@@ -88,12 +97,6 @@ hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStre
 // (kst = k + 1) slot k is the sink's.  grad_sink needs sink_part of
 // sink_chunks(T) * H * n floats.
 int64_t sink_chunks(int64_t T);
-// Appends to long_list (in no particular order) every segment u < *nseg with
-// seg_start[u+1] - seg_start[u] > thresh, counting them in *long_cnt, which
-// must be zero on entry.  max_seg bounds *nseg (sizes the grid).
-hipError_t launch_list_long(const uint32_t* seg_start, const uint32_t* nseg, int64_t max_seg,
-                            uint32_t thresh, uint32_t* long_list, uint32_t* long_cnt,
-                            hipStream_t st);
 hipError_t launch_search_backward(bool bf16, const void* q, const void* subkeys, int64_t T, int H,
                                   int n, int S, int k, int kst, const int64_t* idx, const float* gz,
                                   const float2* qstats, const void* sink, float* grad_q,

@@ -15,9 +15,9 @@
 // atomics, in global memory or in LDS, serialise on them.  Instead the same
 // wave emits one (head, half, sub-key) sort key per group leader, with the
 // group's gradient sum, at the front of its (token, head, half) row of k
-// slots, and counts them; an exclusive scan of the counts places the leaders
-// contiguously (in slot order), and the library's stable radix sort orders
-// those pairs by key.  One wave per segment then sums gsum * q over the
+// slots, and counts them; the library's stable radix sort orders the leaders by
+// key (for many rows an exclusive scan of the counts first places them
+// contiguously, in slot order).  One wave per segment then sums gsum * q over the
 // segment's tokens (in token order; each token's query half is read once) and
 // adds the sum into the sub-key row with one plain read-modify-write: no
 // atomics, bitwise deterministic.  A segment longer than 2048 pairs (a
@@ -403,9 +403,8 @@ __global__ __launch_bounds__(256) void k_sink_reduce(const float* __restrict__ p
 }
 
 // Workspace: keys and group sums per slot (2*T*H*k each), the row counts
-// (scanned in place into offsets, plus the total, plus the count of long
-// segments), the scan's partials, the list of long segments, then the sort of
-// up to 2*T*H*k pairs.
+// (scanned in place into offsets, plus the total), the scan's partials, the
+// list of long segments, then the sort of up to 2*T*H*k pairs.
 static size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 size_t search_backward_ws_bytes(int64_t T, int H, int k) {
   const int64_t rows = 2 * T * H;
@@ -442,15 +441,18 @@ static hipError_t launch_sbwd(const void* q, const void* subkeys, int64_t T_, in
   p += a256((size_t)np * 4);
   float* gvals = reinterpret_cast<float*>(p);
   p += a256((size_t)np * 4);
-  uint32_t* offs = reinterpret_cast<uint32_t*>(p);  // rows + 1, then the long count
+  uint32_t* offs = reinterpret_cast<uint32_t*>(p);  // the row counts, scanned: rows + 1
   p += a256((size_t)(rows + 2) * 4);
   uint32_t* sums = reinterpret_cast<uint32_t*>(p);
   p += a256(scan_scratch_u32(rows + 1) * 4);
   uint32_t* long_list = reinterpret_cast<uint32_t*>(p);
   p += a256((size_t)sbwd_max_long(np) * 4);
   void* sort_ws = p;
-  // the scan's last entry and the count of long segments
-  if (grad_K) e = launch_fill_u32(offs + rows, 0u, 2, st);
+  // Up to SORT_SLOTS_MAX slots are sorted as they lie, the unfilled ones
+  // dropped by the first pass: no scan and no pack (512 tokens, 4 heads,
+  // k = 32: from 18 launches to 8).  More are packed first.
+  const bool slots = np <= SORT_SLOTS_MAX;
+  if (grad_K && !slots) e = launch_fill_u32(offs + rows, 0u, 1, st);  // the scan's last entry
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_search_bwd_q<T>, dim3((unsigned)(((T_ + 3) / 4) * H)), dim3(256), 0, st,
                      (const T*)q, (const T*)subkeys, T_, H, n, S, k, kst, idx, gz,
@@ -458,25 +460,26 @@ static hipError_t launch_sbwd(const void* q, const void* subkeys, int64_t T_, in
                      grad_K ? keys : nullptr, grad_K ? gvals : nullptr, grad_K ? offs : nullptr);
   e = hipGetLastError();
   if (e != hipSuccess || !grad_K) return e;
-  // counts -> offsets; offs[rows] = number of leaders
-  e = scan_exclusive_u32(offs, rows + 1, sums, st);
-  if (e != hipSuccess) return e;
-  uint32_t *kin, *vin;
-  sort_u32_inputs(sort_ws, np, &kin, &vin);
-  hipLaunchKernelGGL(k_sbwd_pack, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, keys, offs,
-                     rows, k, kin, vin);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!slots) {
+    // counts -> offsets; offs[rows] = number of leaders
+    e = scan_exclusive_u32(offs, rows + 1, sums, st);
+    if (e != hipSuccess) return e;
+    uint32_t *kin, *vin;
+    sort_u32_inputs(sort_ws, np, &kin, &vin);
+    hipLaunchKernelGGL(k_sbwd_pack, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, keys, offs,
+                       rows, k, kin, vin);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const uint32_t nbins = (uint32_t)(2 * H) * (uint32_t)S;
   int key_bits = 1;
   while (key_bits < 32 && (uint64_t(1) << key_bits) < nbins) ++key_bits;
-  const uint32_t *ks, *vs, *seg, *nseg;
-  e = sort_u32_segments(np, offs + rows, key_bits, sort_ws, &ks, &vs, &seg, &nseg, st);
+  const uint32_t *ks, *vs, *seg, *nseg, *long_cnt;
+  const SortSrc src{keys, offs, k};
+  e = sort_u32_segments(slots ? &src : nullptr, np, slots ? nullptr : offs + rows, key_bits, sort_ws,
+                        SBWD_LONG, long_list, &ks, &vs, &seg, &nseg, &long_cnt, st);
   if (e != hipSuccess) return e;
   int64_t maxseg = (int64_t)nbins < np ? (int64_t)nbins : np;
-  uint32_t* long_cnt = offs + rows + 1;
-  e = launch_list_long(seg, nseg, maxseg, SBWD_LONG, long_list, long_cnt, st);
-  if (e != hipSuccess) return e;
   int64_t blocks = (maxseg + 3) / 4;
   if (blocks > 16384) blocks = 16384;
   int64_t lblocks = sbwd_max_long(np) < maxseg ? sbwd_max_long(np) : maxseg;

@@ -7,8 +7,11 @@
 //      workgroup per digit), and a stable scatter: each wave ranks a
 //      contiguous quarter of the tile with ballots, and the tile goes out
 //      through LDS in sorted order.  Keys are rows (< 2^26), values lookup ids.
+//      Up to 2^19 keys the passes are a short chain instead (k_chain_*), up to
+//      8192 one workgroup does everything (k_sort_one).
 //   2. Segment heads (first lookup of each distinct row) -> seg_start[U + 1],
-//      the head flags computed where they are counted and placed.
+//      the head flags computed where they are counted and placed; the same
+//      kernel lists the segments longer than a threshold.
 //   3. One lane group per touched row (two adjacent rows per iteration): read
 //      the value row once, then take the contributing lookups in lookup order,
 //      a few at a time with their dy rows loaded together, add w * dy into a
@@ -18,7 +21,7 @@
 //      value and gradient tables are streamed nearly sequentially, and the
 //      result is bitwise deterministic.
 //   4. A row with more than LONG_SEG lookups would hold one lane group for
-//      its whole length: k_list_long lists it, the per-row kernel skips it,
+//      its whole length: it is listed, the per-row kernel skips it,
 //      and a second kernel gives each listed row a workgroup whose lane
 //      groups take contiguous runs of its lookups; their partial sums meet in
 //      LDS and are added in group order (still deterministic).
@@ -36,6 +39,7 @@ constexpr uint32_t LONG_SEG = 1024;  // lookups of a row beyond which it is spli
 constexpr uint32_t LONG_CHUNK = 1024;  // lookups of a long row per workgroup
 constexpr int LONG_WAVES = 8;        // waves of the workgroup that takes a chunk
 constexpr int SCAN_TILE = 256 * SCAN_ITEMS;
+constexpr int64_t SEG_TILES_MAX = 8192;  // tiles whose counts k_seg_place adds up itself
 
 static inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -156,7 +160,8 @@ __global__ __launch_bounds__(256) void k_scan_digits(uint32_t* __restrict__ hist
 }
 
 // ----------------------------------------------------------- radix sort ----
-// KM selects where a pass takes its items: SRC_I64 and SRC_U32 are first
+// KM selects where a pass takes its items: SRC_I64 (an int64 array) and SRC_U32
+// (rows of u32 slots, see SortSrc) are first
 // passes (keys from an int64 or u32 array, values = item positions), SRC_NEXT
 // a later pass (keys and values from the previous pass's output).
 constexpr int SRC_I64 = 0, SRC_U32 = 1, SRC_NEXT = 2;
@@ -311,34 +316,51 @@ __global__ __launch_bounds__(256) void k_seg_count(const uint32_t* __restrict__ 
 
 // Each head i, with u = the number of heads before it, writes seg_start[u] = i;
 // the last item writes seg_start[U] = L and U (the number of segments).
+// scanned: sums holds each tile's first segment number; otherwise the tiles'
+// counts, and the block adds those before it itself (a launch less).  A segment
+// of more than thresh items is listed in long_list (in no particular order:
+// each is then summed on its own).
 __global__ __launch_bounds__(256) void k_seg_place(const uint32_t* __restrict__ keys, int64_t Lmax,
                                                    const uint32_t* __restrict__ Ldev,
-                                                   const uint32_t* __restrict__ sums,
+                                                   const uint32_t* __restrict__ sums, bool scanned,
                                                    uint32_t* __restrict__ seg_start,
-                                                   uint32_t* __restrict__ nseg) {
+                                                   uint32_t* __restrict__ nseg, uint32_t thresh,
+                                                   uint32_t* __restrict__ long_list,
+                                                   uint32_t* __restrict__ long_cnt) {
   __shared__ uint32_t wsum[4];
   const int64_t L = (Ldev && (int64_t)*Ldev < Lmax) ? (int64_t)*Ldev : Lmax;
+  if ((int64_t)blockIdx.x * SCAN_TILE >= L) return;  // nothing in this tile
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+  uint32_t before = 0;
+  if (scanned) {
+    before = sums[blockIdx.x];
+  } else {
+    uint32_t part = 0;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) part += sums[i];
+    block_exclusive_scan(part, wsum, before);
+  }
   uint32_t prev = (base > 0 && base <= L) ? keys[base - 1] : 0u;
-  bool head[SCAN_ITEMS];
+  bool head[SCAN_ITEMS], lng[SCAN_ITEMS];
   uint32_t s = 0;
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i) {
     const int64_t x = base + i;
-    head[i] = false;
+    head[i] = lng[i] = false;
     if (x < L) {
       const uint32_t kx = keys[x];
       head[i] = (x == 0 || kx != prev);
+      lng[i] = head[i] && x + thresh < L && keys[x + thresh] == kx;
       prev = kx;
     }
     s += head[i] ? 1u : 0u;
   }
   uint32_t total;
-  uint32_t run = sums[blockIdx.x] + block_exclusive_scan(s, wsum, total);
+  uint32_t run = before + block_exclusive_scan(s, wsum, total);
 #pragma unroll
   for (int i = 0; i < SCAN_ITEMS; ++i) {
     const int64_t x = base + i;
     if (head[i]) seg_start[run] = (uint32_t)x;
+    if (lng[i]) long_list[atomicAdd(long_cnt, 1u)] = run;
     run += head[i] ? 1u : 0u;
     if (x == L - 1) {
       seg_start[run] = (uint32_t)L;
@@ -347,6 +369,333 @@ __global__ __launch_bounds__(256) void k_seg_place(const uint32_t* __restrict__ 
   }
 }
 
+// ------------------------------------------------------- few keys ----
+// Up to CHAIN_MAX keys a radix pass of three launches is mostly launches and
+// the latency of 16 serial rounds per wave on a few workgroups (65536 keys:
+// 6 + 4 + 15 us a pass).  The chain takes one launch per pass after a first
+// histogram: workgroups of 16 waves with 4 rounds each; every scatter adds up
+// the tile counts before its own itself (at most 128 tiles) and counts the next
+// pass's digits of the tiles it writes to with integer atomics (the counts
+// cleared by the first launch).  The result is the same stable sort.
+constexpr int CHAIN_ITEMS = 4;                       // keys per thread
+constexpr int CHAIN_TILE = 1024 * CHAIN_ITEMS;
+constexpr int ONE_ITEMS = 8;
+constexpr int64_t ONE_MAX = 1024 * ONE_ITEMS;        // keys one workgroup sorts by itself
+constexpr int64_t CHAIN_MAX = (int64_t)1 << 19;
+static_assert(SORT_SLOTS_MAX == CHAIN_MAX, "slot rows are sorted by the chain or one workgroup");
+
+// Where a sort takes its items: item i of an int64 or u32 array (value: the
+// position), or slot i of rows of k u32 keys of which row r fills its first
+// counts[r] (the others are dropped; value: the slot).
+template <int KM>
+__device__ __forceinline__ bool first_key(const SortSrc& src, int64_t i, int64_t L, uint32_t& key) {
+  if constexpr (KM == SRC_I64) {
+    if (i >= L) return false;
+    key = (uint32_t)reinterpret_cast<const int64_t*>(src.keys)[i];
+    return true;
+  } else {
+    if (i >= L) return false;
+    const uint32_t r = (uint32_t)i / (uint32_t)src.k;
+    if ((uint32_t)i - r * (uint32_t)src.k >= src.counts[r]) return false;
+    key = reinterpret_cast<const uint32_t*>(src.keys)[i];
+    return true;
+  }
+}
+
+// Exclusive scan over the first 256 threads of a workgroup (thread = digit) of
+// their v; every thread of the workgroup takes part.
+__device__ __forceinline__ uint32_t scan_digits256(uint32_t v, uint32_t* wsum, uint32_t& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t x = v;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, WAVE);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63 && wave < 4) wsum[wave] = x;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave && w < 4; ++w) before += wsum[w];
+  total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  __syncthreads();
+  return before + x - v;
+}
+
+template <int KM>
+__global__ __launch_bounds__(1024) void k_chain_hist(SortSrc src, int64_t L, int bits, int passes,
+                                                     uint32_t* __restrict__ hist,
+                                                     uint32_t* __restrict__ misc) {
+  __shared__ uint32_t h[RADIX];
+  const int tid = threadIdx.x;
+  if (tid < RADIX) h[tid] = 0;
+  if (blockIdx.x == 0 && tid < 4) misc[tid] = 0;
+  __syncthreads();
+  const uint32_t mask = (1u << bits) - 1u;
+#pragma unroll
+  for (int i = 0; i < CHAIN_ITEMS; ++i) {
+    uint32_t key;
+    if (first_key<KM>(src, (int64_t)blockIdx.x * CHAIN_TILE + i * 1024 + tid, L, key))
+      atomicAdd(&h[key & mask], 1u);
+  }
+  __syncthreads();
+  if (tid < RADIX) {
+    const int64_t at = (int64_t)blockIdx.x * RADIX + tid;
+    hist[at] = h[tid];
+    for (int p = 1; p < passes; ++p) hist[(int64_t)p * gridDim.x * RADIX + at] = 0;
+  }
+}
+
+// One stable pass.  hist: this pass's counts per (tile, digit); hist_next (null
+// on the last pass): the next pass's, with next_bits digits.  Ldev: the item
+// count of a later pass (null: L).  The first pass writes it to total_out.
+template <int KM>
+__global__ __launch_bounds__(1024) void k_chain_scatter(
+    SortSrc src, const uint32_t* __restrict__ vals_in, int64_t L, const uint32_t* __restrict__ Ldev,
+    int shift, int bits, int next_bits, const uint32_t* __restrict__ hist,
+    uint32_t* __restrict__ hist_next, uint32_t* __restrict__ keys_out,
+    uint32_t* __restrict__ vals_out, uint32_t* __restrict__ total_out) {
+  constexpr int PER_WAVE = CHAIN_ITEMS * WAVE;
+  __shared__ uint32_t red[2][4][RADIX];
+  __shared__ uint32_t run[RADIX], tstart[RADIX];
+  __shared__ uint32_t wcnt[16][RADIX];
+  __shared__ uint32_t wsum[4];
+  __shared__ uint32_t skey[CHAIN_TILE], sval[CHAIN_TILE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nblk = gridDim.x;
+  if (Ldev) L = *Ldev;
+  const int64_t tile = (int64_t)blockIdx.x * CHAIN_TILE;
+  if (tile >= L) return;  // whole block (block 0 never, unless there is nothing)
+  const int64_t wbase = tile + (int64_t)wave * PER_WAVE;
+  uint32_t key[CHAIN_ITEMS], val[CHAIN_ITEMS], rk[CHAIN_ITEMS];
+  bool valid[CHAIN_ITEMS];
+#pragma unroll
+  for (int i = 0; i < CHAIN_ITEMS; ++i) {
+    const int64_t pos = wbase + i * WAVE + lane;
+    key[i] = 0;
+    if constexpr (KM == SRC_NEXT) {
+      valid[i] = pos < L;
+      if (valid[i]) key[i] = reinterpret_cast<const uint32_t*>(src.keys)[pos];
+      val[i] = valid[i] ? vals_in[pos] : 0u;
+    } else {
+      valid[i] = first_key<KM>(src, pos, L, key[i]);
+      val[i] = (uint32_t)pos;
+    }
+  }
+  {  // digit tid & 255, every fourth tile: all its keys, and those of earlier tiles
+    const int d = tid & 255, qd = tid >> 8;
+    uint32_t tot = 0, pre = 0;
+#pragma unroll 8
+    for (int b = qd; b < nblk; b += 4) {
+      const uint32_t v = hist[(int64_t)b * RADIX + d];
+      tot += v;
+      pre += b < (int)blockIdx.x ? v : 0u;
+    }
+    red[0][qd][d] = tot;
+    red[1][qd][d] = pre;
+  }
+#pragma unroll
+  for (int i = 0; i < 16 * RADIX / 1024; ++i) (&wcnt[0][0])[i * 1024 + tid] = 0;
+  __syncthreads();
+  {
+    uint32_t tot = 0, pre = 0, all;
+    if (tid < RADIX) {
+      tot = red[0][0][tid] + red[0][1][tid] + red[0][2][tid] + red[0][3][tid];
+      pre = red[1][0][tid] + red[1][1][tid] + red[1][2][tid] + red[1][3][tid];
+    }
+    const uint32_t dbase = scan_digits256(tot, wsum, all);
+    if (tid < RADIX) run[tid] = dbase + pre;
+    if (total_out && blockIdx.x == 0 && tid == 0) *total_out = all;
+  }
+  const uint32_t mask = (1u << bits) - 1u;
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < CHAIN_ITEMS; ++i) {
+    const uint32_t dig = (key[i] >> shift) & mask;
+    uint64_t peers = __ballot(valid[i]);
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (dig >> b) & 1u;
+      const uint64_t set = __ballot(bit);
+      peers &= bit ? set : ~set;
+    }
+    const uint32_t r = (uint32_t)__popcll(peers & below);
+    rk[i] = wcnt[wave][dig] + r;
+    if (valid[i] && r == 0) wcnt[wave][dig] += (uint32_t)__popcll(peers);
+  }
+  __syncthreads();
+  uint32_t n;  // items of this tile
+  {
+    uint32_t cnt = 0;
+    if (tid < RADIX)
+      for (int w = 0; w < 16; ++w) cnt += wcnt[w][tid];
+    const uint32_t st = scan_digits256(cnt, wsum, n);
+    if (tid < RADIX) {
+      tstart[tid] = st;
+      uint32_t at = st;
+      for (int w = 0; w < 16; ++w) {
+        const uint32_t c = wcnt[w][tid];
+        wcnt[w][tid] = at;
+        at += c;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < CHAIN_ITEMS; ++i)
+    if (valid[i]) {
+      const uint32_t p = wcnt[wave][(key[i] >> shift) & mask] + rk[i];
+      skey[p] = key[i];
+      sval[p] = val[i];
+    }
+  __syncthreads();
+  const uint32_t nmask = (1u << next_bits) - 1u;
+  const int tbits = 32 - __builtin_clz((uint32_t)nblk);
+  for (uint32_t e0 = 0; e0 < n; e0 += 1024) {
+    const uint32_t e = e0 + tid;
+    const bool in = e < n;
+    const uint32_t kk = in ? skey[e] : 0u;
+    const uint32_t dig = (kk >> shift) & mask;
+    const uint32_t dst = in ? run[dig] + e - tstart[dig] : 0u;
+    if (in) {
+      keys_out[dst] = kk;
+      vals_out[dst] = sval[e];
+    }
+    if (hist_next) {  // one atomic per distinct (tile, digit) of the wave: few hot ones
+                      // (a sub-key table's upper digits, a sink row) serialise otherwise
+      const uint32_t at = (dst / CHAIN_TILE) * RADIX + ((kk >> (shift + bits)) & nmask);
+      uint64_t peers = __ballot(in);
+      for (int b = 0; b < next_bits; ++b) {
+        const bool bit = (at >> b) & 1u;
+        const uint64_t set = __ballot(bit);
+        peers &= bit ? set : ~set;
+      }
+      for (int b = RADIX_BITS; b < RADIX_BITS + tbits; ++b) {
+        const bool bit = (at >> b) & 1u;
+        const uint64_t set = __ballot(bit);
+        peers &= bit ? set : ~set;
+      }
+      if (in && (peers & below) == 0) atomicAdd(&hist_next[at], (uint32_t)__popcll(peers));
+    }
+  }
+}
+
+// All passes, the segments and the long list of up to ONE_MAX keys by one
+// workgroup, the keys in LDS between the passes.
+template <int KM>
+__global__ __launch_bounds__(1024) void k_sort_one(SortSrc src, int L, int key_bits,
+                                                   uint32_t* __restrict__ keys_out,
+                                                   uint32_t* __restrict__ vals_out,
+                                                   uint32_t* __restrict__ seg_start,
+                                                   uint32_t* __restrict__ misc, uint32_t thresh,
+                                                   uint32_t* __restrict__ long_list,
+                                                   uint32_t* __restrict__ long_cnt) {
+  __shared__ uint32_t wcnt[16][RADIX];
+  __shared__ uint32_t wsum[16];
+  __shared__ uint32_t skey[ONE_MAX], sval[ONE_MAX];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+  if (tid == 0) *long_cnt = 0;
+  uint32_t key[ONE_ITEMS], val[ONE_ITEMS], rk[ONE_ITEMS];
+  bool valid[ONE_ITEMS];
+  for (int shift = 0; shift < key_bits; shift += RADIX_BITS) {
+    const int bits = key_bits - shift < RADIX_BITS ? key_bits - shift : RADIX_BITS;
+    const uint32_t mask = (1u << bits) - 1u;
+    // wave w takes the w-th run of whole 64s, as few rounds as the count needs
+    const int rounds = (L + 1023) / 1024;
+    const int wbase = wave * rounds * WAVE;
+#pragma unroll
+    for (int i = 0; i < ONE_ITEMS; ++i) {
+      const int pos = wbase + i * WAVE + lane;
+      key[i] = val[i] = 0;
+      valid[i] = false;
+      if (i < rounds) {
+        if (shift == 0) {
+          valid[i] = first_key<KM>(src, pos, L, key[i]);
+          val[i] = (uint32_t)pos;
+        } else if (pos < L) {
+          valid[i] = true;
+          key[i] = skey[pos];
+          val[i] = sval[pos];
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16 * RADIX / 1024; ++i) (&wcnt[0][0])[i * 1024 + tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ONE_ITEMS; ++i) {
+      if (i >= rounds) break;  // the same for the whole workgroup
+      const uint32_t dig = (key[i] >> shift) & mask;
+      uint64_t peers = __ballot(valid[i]);
+      for (int b = 0; b < bits; ++b) {
+        const bool bit = (dig >> b) & 1u;
+        const uint64_t set = __ballot(bit);
+        peers &= bit ? set : ~set;
+      }
+      const uint32_t r = (uint32_t)__popcll(peers & below);
+      rk[i] = wcnt[wave][dig] + r;
+      if (valid[i] && r == 0) wcnt[wave][dig] += (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t n;
+    {
+      uint32_t cnt = 0;
+      if (tid < RADIX)
+        for (int w = 0; w < 16; ++w) cnt += wcnt[w][tid];
+      uint32_t at = scan_digits256(cnt, wsum, n);
+      if (tid < RADIX)
+        for (int w = 0; w < 16; ++w) {
+          const uint32_t c = wcnt[w][tid];
+          wcnt[w][tid] = at;
+          at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ONE_ITEMS; ++i)
+      if (valid[i]) {
+        const uint32_t p = wcnt[wave][(key[i] >> shift) & mask] + rk[i];
+        skey[p] = key[i];
+        sval[p] = val[i];
+      }
+    L = (int)n;  // dropped slots are gone after the first pass
+    __syncthreads();
+  }
+  for (int i = tid; i < L; i += 1024) {
+    keys_out[i] = skey[i];
+    vals_out[i] = sval[i];
+  }
+  // segments: thread t takes items [t * per, (t + 1) * per)
+  const int per = (L + 1023) / 1024;
+  const int i0 = tid * per < L ? tid * per : L, i1 = i0 + per < L ? i0 + per : L;
+  uint32_t heads = 0;
+  for (int i = i0; i < i1; ++i) heads += (i == 0 || skey[i] != skey[i - 1]) ? 1u : 0u;
+  uint32_t x = heads;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, WAVE);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  uint32_t u = x - heads;
+  for (int w = 0; w < wave; ++w) u += wsum[w];
+  for (int i = i0; i < i1; ++i) {
+    const uint32_t kx = skey[i];
+    if (i == 0 || kx != skey[i - 1]) {
+      seg_start[u] = (uint32_t)i;
+      if (i + thresh < (uint32_t)L && skey[i + thresh] == kx) long_list[atomicAdd(long_cnt, 1u)] = u;
+      ++u;
+    }
+    if (i == L - 1) {
+      seg_start[u] = (uint32_t)L;
+      misc[0] = u;
+    }
+  }
+  if (L == 0 && tid == 0) {
+    seg_start[0] = 0;
+    misc[0] = 0;
+  }
+}
 
 // ------------------------------------------------------- per-row backward ----
 // One lane group per touched row.  A row with more than LONG_SEG lookups is
@@ -548,70 +897,121 @@ size_t long_partial_bytes(int64_t L, int D) {
   return align256((size_t)(L / LONG_CHUNK + max_long(L)) * (size_t)D * sizeof(float));
 }
 
-// Stable LSD radix sort of L keys (< 2^key_bits, from an int64 or a u32 array)
-// with their positions as values, then the segment starts of equal keys:
-// seg[0..U] in b.seg, U in b.misc[0].  *ks / *vs receive the sorted arrays.
-// L is the item count, or its upper bound when Ldev (device memory) holds the
-// count; vals_in, if given, are the first pass's values (else positions).
-static hipError_t sort_segments(const void* keys, bool key64, int64_t L, int key_bits,
-                                const SortedWs& b, const uint32_t** ks, const uint32_t** vs,
-                                hipStream_t st, const uint32_t* vals_in = nullptr,
+// Stable LSD radix sort of the source's keys (< 2^key_bits) with their
+// positions (or vals_in) as values, then the segment starts of equal keys:
+// seg[0..U] in b.seg, U in b.misc[0]; the segments of more than thresh items in
+// long_list, their number in b.misc[1].  *ks / *vs receive the sorted arrays.
+// L is the item count, or its upper bound: of slots, or of items when Ldev
+// (device memory) holds their count.
+static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, const SortedWs& b,
+                                uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
+                                const uint32_t** vs, hipStream_t st,
+                                const uint32_t* vals_in = nullptr,
                                 const uint32_t* Ldev = nullptr) {
-  hipError_t e = hipSuccess;
-  const int64_t nblk = cdiv(L, SORT_TILE);
-  const void* kin = keys;
-  const uint32_t* vin = vals_in;
+  const bool slots = src.counts != nullptr;
+  const bool key64 = !slots && !vals_in;
   uint32_t *kout = b.keys_a, *vout = b.vals_a;
-  for (int shift = 0, pass = 0; shift < key_bits; shift += RADIX_BITS, ++pass) {
-    const int bits = (key_bits - shift) < RADIX_BITS ? (key_bits - shift) : RADIX_BITS;
-    const dim3 g((unsigned)nblk), blk(256);
-    if (pass > 0 || vals_in)
-      hipLaunchKernelGGL(k_radix_hist<SRC_NEXT>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
-    else if (key64)
-      hipLaunchKernelGGL(k_radix_hist<SRC_I64>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
+  if ((key64 || slots) && L <= ONE_MAX) {
+    *ks = kout;
+    *vs = vout;
+    if (slots)
+      hipLaunchKernelGGL(k_sort_one<SRC_U32>, dim3(1), dim3(1024), 0, st, src, (int)L, key_bits, kout,
+                         vout, b.seg, b.misc, thresh, long_list, b.misc + 1);
     else
-      hipLaunchKernelGGL(k_radix_hist<SRC_U32>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
-    hipLaunchKernelGGL(k_scan_digits, dim3(RADIX), blk, 0, st, b.hist, nblk, b.totals);
-    if (pass > 0 || vals_in)
-      hipLaunchKernelGGL(k_radix_scatter<SRC_NEXT>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
-    else if (key64)
-      hipLaunchKernelGGL(k_radix_scatter<SRC_I64>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
-    else
-      hipLaunchKernelGGL(k_radix_scatter<SRC_U32>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
-    kin = kout;
-    vin = vout;
-    if (kout == b.keys_a) { kout = b.keys_b; vout = b.vals_b; }
-    else { kout = b.keys_a; vout = b.vals_a; }
+      hipLaunchKernelGGL(k_sort_one<SRC_I64>, dim3(1), dim3(1024), 0, st, src, (int)L, key_bits, kout,
+                         vout, b.seg, b.misc, thresh, long_list, b.misc + 1);
+    return hipGetLastError();
   }
-  *ks = reinterpret_cast<const uint32_t*>(kin);
-  *vs = vin;
+  const int passes = (key_bits + RADIX_BITS - 1) / RADIX_BITS;
+  if ((key64 || slots) && L <= CHAIN_MAX) {
+    const int64_t nblk = cdiv(L, CHAIN_TILE);  // up to four histograms fit b.hist: 1024 * nblk <= L
+    const dim3 g((unsigned)nblk), blk(1024);
+    const int bits0 = key_bits < RADIX_BITS ? key_bits : RADIX_BITS;
+    if (slots)
+      hipLaunchKernelGGL(k_chain_hist<SRC_U32>, g, blk, 0, st, src, L, bits0, passes, b.hist, b.misc);
+    else
+      hipLaunchKernelGGL(k_chain_hist<SRC_I64>, g, blk, 0, st, src, L, bits0, passes, b.hist, b.misc);
+    SortSrc in = src;
+    const uint32_t* vin = nullptr;
+    for (int p = 0; p < passes; ++p) {
+      const int shift = p * RADIX_BITS;
+      auto width = [&](int q) { return key_bits - q * RADIX_BITS < RADIX_BITS ? key_bits - q * RADIX_BITS : RADIX_BITS; };
+      const uint32_t* hist = b.hist + (int64_t)p * nblk * RADIX;
+      uint32_t* next = p + 1 < passes ? b.hist + (int64_t)(p + 1) * nblk * RADIX : nullptr;
+      const int nbits = next ? width(p + 1) : 1;
+      const uint32_t* count = p > 0 ? b.misc + 3 : nullptr;
+      uint32_t* total = p == 0 ? b.misc + 3 : nullptr;
+      if (p > 0)
+        hipLaunchKernelGGL(k_chain_scatter<SRC_NEXT>, g, blk, 0, st, in, vin, L, count, shift, width(p), nbits, hist, next, kout, vout, total);
+      else if (slots)
+        hipLaunchKernelGGL(k_chain_scatter<SRC_U32>, g, blk, 0, st, in, vin, L, count, shift, width(p), nbits, hist, next, kout, vout, total);
+      else
+        hipLaunchKernelGGL(k_chain_scatter<SRC_I64>, g, blk, 0, st, in, vin, L, count, shift, width(p), nbits, hist, next, kout, vout, total);
+      in = SortSrc{kout, nullptr, 0};
+      vin = vout;
+      if (kout == b.keys_a) { kout = b.keys_b; vout = b.vals_b; }
+      else { kout = b.keys_a; vout = b.vals_a; }
+    }
+    *ks = reinterpret_cast<const uint32_t*>(in.keys);
+    *vs = vin;
+    Ldev = b.misc + 3;
+  } else {
+    hipError_t e = launch_fill_u32(b.misc, 0u, 2, st);
+    if (e != hipSuccess) return e;
+    const int64_t nblk = cdiv(L, SORT_TILE);
+    const void* kin = src.keys;
+    const uint32_t* vin = vals_in;
+    for (int shift = 0, pass = 0; shift < key_bits; shift += RADIX_BITS, ++pass) {
+      const int bits = (key_bits - shift) < RADIX_BITS ? (key_bits - shift) : RADIX_BITS;
+      const dim3 g((unsigned)nblk), blk(256);
+      if (pass > 0 || vals_in)
+        hipLaunchKernelGGL(k_radix_hist<SRC_NEXT>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
+      else
+        hipLaunchKernelGGL(k_radix_hist<SRC_I64>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
+      hipLaunchKernelGGL(k_scan_digits, dim3(RADIX), blk, 0, st, b.hist, nblk, b.totals);
+      if (pass > 0 || vals_in)
+        hipLaunchKernelGGL(k_radix_scatter<SRC_NEXT>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
+      else
+        hipLaunchKernelGGL(k_radix_scatter<SRC_I64>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
+      kin = kout;
+      vin = vout;
+      if (kout == b.keys_a) { kout = b.keys_b; vout = b.vals_b; }
+      else { kout = b.keys_a; vout = b.vals_a; }
+    }
+    *ks = reinterpret_cast<const uint32_t*>(kin);
+    *vs = vin;
+  }
   const int64_t nb = cdiv(L, SCAN_TILE);
+  const bool scanned = nb > SEG_TILES_MAX;
   hipLaunchKernelGGL(k_seg_count, dim3((unsigned)nb), dim3(256), 0, st, *ks, L, Ldev, b.sums);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, b.sums, nb);
-  hipLaunchKernelGGL(k_seg_place, dim3((unsigned)nb), dim3(256), 0, st, *ks, L, Ldev, b.sums, b.seg,
-                     b.misc);
+  if (scanned) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, b.sums, nb);
+  hipLaunchKernelGGL(k_seg_place, dim3((unsigned)nb), dim3(256), 0, st, *ks, L, Ldev, b.sums, scanned,
+                     b.seg, b.misc, thresh, long_list, b.misc + 1);
   return hipGetLastError();
 }
 
-// Sort of u32 keys with u32 values for other kernels of the library: up to
-// Lmax items, their count in device memory (*Ldev).  The input arrays must be
-// the ones sort_u32_inputs returns for this workspace (the first radix pass
-// reads them, the second overwrites them).
+// Sort of u32 keys for other kernels of the library: either up to
+// SORT_SLOTS_MAX slots in rows of k with their counts (values: the slots), or
+// up to Lmax (key, value) pairs, their count in device memory (*Ldev), in the
+// arrays sort_u32_inputs returns for this workspace (the first radix pass reads
+// them, the second overwrites them).
 void sort_u32_inputs(void* ws, int64_t Lmax, uint32_t** keys_in, uint32_t** vals_in) {
   SortedWs b = carve(ws, Lmax);
   *keys_in = b.keys_b;
   *vals_in = b.vals_b;
 }
 
-hipError_t sort_u32_segments(int64_t Lmax, const uint32_t* Ldev, int key_bits, void* ws,
-                             const uint32_t** ks, const uint32_t** vs, const uint32_t** seg,
-                             const uint32_t** nseg, hipStream_t st) {
+hipError_t sort_u32_segments(const SortSrc* slots, int64_t Lmax, const uint32_t* Ldev, int key_bits,
+                             void* ws, uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
+                             const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
+                             const uint32_t** nlong, hipStream_t st) {
   SortedWs b = carve(ws, Lmax);
   *seg = b.seg;
   *nseg = b.misc;
-  hipError_t e = launch_fill_u32(b.misc, 0u, 1, st);
-  if (e != hipSuccess || Lmax == 0) return e;
-  return sort_segments(b.keys_b, false, Lmax, key_bits, b, ks, vs, st, b.vals_b, Ldev);
+  *nlong = b.misc + 1;
+  if (slots) return sort_segments(*slots, Lmax, key_bits, b, thresh, long_list, ks, vs, st);
+  return sort_segments(SortSrc{b.keys_b, nullptr, 0}, Lmax, key_bits, b, thresh, long_list, ks, vs, st,
+                       b.vals_b, Ldev);
 }
 
 // Exclusive prefix sum of n u32 in place; sums needs scan_scratch_u32(n) entries.
@@ -620,30 +1020,7 @@ hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStre
   return exclusive_scan(data, n, sums, st);
 }
 
-// Segments longer than LONG_SEG lookups, listed (in no particular order: each
-// is then summed on its own) for k_bag_bwd_long; k_bag_bwd_rows skips them.
-__global__ __launch_bounds__(256) void k_list_long(const uint32_t* __restrict__ seg_start,
-                                                   const uint32_t* __restrict__ nseg,
-                                                   uint32_t thresh,
-                                                   uint32_t* __restrict__ long_list,
-                                                   uint32_t* __restrict__ long_cnt) {
-  const uint32_t U = *nseg;
-  for (uint32_t u = blockIdx.x * 256 + threadIdx.x; u < U; u += gridDim.x * 256)
-    if (seg_start[u + 1] - seg_start[u] > thresh) long_list[atomicAdd(long_cnt, 1u)] = u;
-}
-
-hipError_t launch_list_long(const uint32_t* seg_start, const uint32_t* nseg, int64_t max_seg,
-                            uint32_t thresh, uint32_t* long_list, uint32_t* long_cnt,
-                            hipStream_t st) {
-  int64_t gb = cdiv(max_seg, 256);
-  if (gb > 2048) gb = 2048;
-  if (gb < 1) gb = 1;
-  hipLaunchKernelGGL(k_list_long, dim3((unsigned)gb), dim3(256), 0, st, seg_start, nseg, thresh,
-                     long_list, long_cnt);
-  return hipGetLastError();
-}
-
-// Rows listed by k_list_long (more than LONG_SEG lookups) are cut into chunks
+// Rows listed with the segments (more than LONG_SEG lookups) are cut into chunks
 // of LONG_CHUNK consecutive lookups (in lookup order), and every chunk of
 // every listed row is summed by a workgroup of its own, so a row chosen by a
 // large share of the tokens is spread over many CUs:
@@ -825,8 +1202,8 @@ hipError_t launch_bag_backward_sorted(bool bf16, const void* dy, const void* val
   const int64_t L = T * bag;
   SortedWs b = carve(ws, L);
   if (num_rows_dev) *num_rows_dev = b.misc;
-  hipError_t e = launch_fill_u32(b.misc, 0u, 2, st);
-  if (e != hipSuccess || L == 0) return e;
+  if (L == 0) return launch_fill_u32(b.misc, 0u, 2, st);
+  hipError_t e = hipSuccess;
   const uint32_t* ks = nullptr;
   const uint32_t* vs = nullptr;
 
@@ -835,7 +1212,8 @@ hipError_t launch_bag_backward_sorted(bool bf16, const void* dy, const void* val
     LaunchTimer lt_sort("sort_by_row", st);
     int key_bits = 1;
     while (key_bits < 32 && (int64_t(1) << key_bits) < N) ++key_bits;
-    e = sort_segments(idx, true, L, key_bits, b, &ks, &vs, st);
+    e = sort_segments(SortSrc{idx, nullptr, 0}, L, key_bits, b, (uint32_t)LONG_SEG, b.long_list, &ks,
+                      &vs, st);
     if (e != hipSuccess) return e;
   }
 
@@ -850,8 +1228,6 @@ hipError_t launch_bag_backward_sorted(bool bf16, const void* dy, const void* val
   int64_t rblocks = max_long(L);
   if (rblocks > 512) rblocks = 512;
   const int ngrp_cap = 16384 / D;  // partial rows that fit 64 KiB
-  e = launch_list_long(b.seg, b.misc, L, (uint32_t)LONG_SEG, b.long_list, b.misc + 1, st);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_long_bases, dim3(1), dim3(256), 0, st, (const uint32_t*)b.seg,
                      (const uint32_t*)b.long_list, (const uint32_t*)(b.misc + 1), b.long_base);
   LaunchTimer lt("bag_backward_rows", st);
