@@ -82,7 +82,7 @@ struct SortSrc {
   const uint32_t* counts;
   int k;
 };
-constexpr int64_t SORT_SLOTS_MAX = (int64_t)1 << 19;  // slots a sort takes as they are
+constexpr int64_t SORT_SLOTS_MAX = (int64_t)1 << 21;  // slots a sort takes as they are
 void sort_u32_inputs(void* ws, int64_t Lmax, uint32_t** keys_in, uint32_t** vals_in);
 hipError_t sort_u32_segments(const SortSrc* slots, int64_t Lmax, const uint32_t* Ldev, int key_bits,
                              void* ws, uint32_t thresh, uint32_t* long_list, const uint32_t** ks,

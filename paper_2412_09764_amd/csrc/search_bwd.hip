@@ -28,6 +28,7 @@
 
 namespace pk {
 
+// k > 32 (k_search_bwd_q32 below otherwise):
 // Per (token, head) wave, per half: lane j holds rank j's sub-key; each lane
 // finds the ranks sharing its sub-key (one ballot per index bit), the lowest
 // of them leads the group and adds the group's gradients in rank order.  Then
@@ -182,6 +183,163 @@ __global__ __launch_bounds__(256) void k_search_bwd_q(const T* __restrict__ q,
   }
 }
 
+// 16 bytes of a query or sub-key half row.
+template <typename T>
+struct Seg16;
+template <>
+struct Seg16<uint16_t> {
+  static constexpr int N = 8;
+  uint4 raw;
+  __device__ __forceinline__ void load(const uint16_t* p) { raw = ld16(p); }
+  __device__ __forceinline__ void to_f32(float* v) const {
+    v[0] = bf16_lo(raw.x); v[1] = bf16_hi(raw.x); v[2] = bf16_lo(raw.y); v[3] = bf16_hi(raw.y);
+    v[4] = bf16_lo(raw.z); v[5] = bf16_hi(raw.z); v[6] = bf16_lo(raw.w); v[7] = bf16_hi(raw.w);
+  }
+};
+template <>
+struct Seg16<float> {
+  static constexpr int N = 4;
+  uint4 raw;
+  __device__ __forceinline__ void load(const float* p) { raw = ld16(p); }
+  __device__ __forceinline__ void to_f32(float* v) const {
+    v[0] = __uint_as_float(raw.x); v[1] = __uint_as_float(raw.y);
+    v[2] = __uint_as_float(raw.z); v[3] = __uint_as_float(raw.w);
+  }
+};
+
+// k_search_bwd_q for k <= 32, where a half wave holds all ranks: lanes 0-31
+// work on half 0 and lanes 32-63 on half 1 through every step, so the grouping
+// is done once instead of twice (with 32-bit masks), and a sub-key row is read
+// by 32 lanes of 16 bytes, a row of each half per instruction.  The kernel is
+// bound by its vector instructions, not by the row reads from L2: 1052 per wave
+// and 231 us as two passes (32768 tokens, 4 heads, S = 2048, k = 32), 694 and
+// 176 us like this.  Every sum is the other form's, in its order.
+template <typename T>
+__global__ __launch_bounds__(256) void k_search_bwd_q32(
+    const T* __restrict__ q, const T* __restrict__ subkeys, int64_t ntok, int H, int n, int S,
+    int k, int kst, const int64_t* __restrict__ idx, const float* __restrict__ gz,
+    const T* __restrict__ sink, const float2* __restrict__ qstats, float* __restrict__ grad_q,
+    uint32_t* __restrict__ keys, float* __restrict__ gvals, uint32_t* __restrict__ counts) {
+  using Seg = Seg16<T>;
+  constexpr int N = Seg::N;
+  constexpr int QU = PK_SBWD_QU;
+  __shared__ uint2 list[4][2][32];  // the leaders' (sub-key, gradient sum bits), per half
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int p = lane >> 5, j = lane & 31;
+  const int h = (int)(blockIdx.x % (unsigned)H);
+  const int64_t t = (int64_t)(blockIdx.x / (unsigned)H) * 4 + wave;
+  if (t >= ntok) return;
+  const int d = n >> 1;
+  const size_t r = (size_t)t * H + h;
+  const int64_t ix = j < k ? idx[r * kst + j] : -1;
+  const bool okl = ix >= 0 && ix < (int64_t)S * S;
+  // the half's sub-key index (S * S <= 2^26: a 32-bit division)
+  const uint32_t ix1 = okl ? (uint32_t)ix / (uint32_t)S : 0u;
+  const int mine = okl ? (int)(p == 0 ? ix1 : (uint32_t)ix - ix1 * (uint32_t)S) : -1;
+  const float g = okl ? gz[r * kst + j] : 0.f;
+  const uint32_t below = (1u << j) - 1u;
+  const int nbits = S > 1 ? 32 - __builtin_clz((unsigned)(S - 1)) : 0;  // bits of a sub-key index
+  auto of_half = [&](uint64_t m) { return p == 0 ? (uint32_t)m : (uint32_t)(m >> 32); };
+  // the ranks of this half sharing the lane's sub-key
+  uint32_t peers = of_half(__ballot(okl));
+  for (int bt = 0; bt < nbits; ++bt) {
+    const int bit = __builtin_amdgcn_sbfe(mine, bt, 1);  // 0 or -1
+    peers &= ~(of_half(__ballot(bit != 0)) ^ (uint32_t)bit);
+  }
+  const bool leader = okl && (peers & below) == 0u;
+  // the leader's group sum, in rank order (the leader is its group's first); a
+  // lane with nothing left takes a value it drops
+  float gsum = g;
+  uint32_t pm = leader ? peers & (peers - 1u) : 0u;
+  while (__ballot(pm != 0u) != 0ull) {
+    const int v = __builtin_amdgcn_ds_bpermute((p << 7) + (__builtin_ctz(pm | 0x80000000u) << 2),
+                                               __float_as_int(g));
+    gsum += pm != 0u ? __int_as_float(v) : 0.f;
+    pm &= pm - 1u;
+  }
+  const uint64_t lm = __ballot(leader);
+  const uint32_t lmh = of_half(lm);
+  const uint32_t pos = (uint32_t)__builtin_popcount(lmh & below);
+  const uint32_t cnt = (uint32_t)__builtin_popcount(lmh);
+  if (keys) {
+    const size_t rp = r * 2 + p;
+    if (leader) {
+      keys[rp * k + pos] = (uint32_t)(h * 2 + p) * (uint32_t)S + (uint32_t)mine;
+      gvals[rp * k + pos] = gsum;
+    }
+    if (j == 0) counts[rp] = cnt;
+  }
+  if (!grad_q) return;
+  const int e0 = j * N;
+  const bool has = e0 < d;
+  const int eo = has ? e0 : 0;
+  // The leaders first, as byte offsets into the head's two tables (at most
+  // 2 * 8192 rows of 512 bytes), then row 0 of the half with weight 0: a row
+  // costs an LDS read at a constant offset and one addition.
+  const uint32_t row_bytes = (uint32_t)d * (uint32_t)sizeof(T);
+  const uint32_t half0 = p == 0 ? 0u : (uint32_t)S * row_bytes;
+  list[wave][p][leader ? pos : cnt + (uint32_t)j - pos] =
+      make_uint2(leader ? half0 + (uint32_t)mine * row_bytes : half0,
+                 leader ? __float_as_uint(gsum) : 0u);
+  const char* const kb = reinterpret_cast<const char*>(subkeys + (size_t)(h * 2) * S * d);
+  const uint32_t lo = (uint32_t)eo * (uint32_t)sizeof(T);
+  const uint32_t n0 = (uint32_t)__popcll(lm & 0xFFFFFFFFull), n1 = (uint32_t)__popcll(lm >> 32);
+  const uint32_t rows = n0 > n1 ? n0 : n1;  // uniform
+  float acc[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = 0.f;
+  static_assert(32 % QU == 0, "batches of the 32 list entries");
+  for (uint32_t b = 0; b < rows; b += QU) {
+    Seg ks[QU];
+    uint2 e[QU];
+#pragma unroll
+    for (int u = 0; u < QU; ++u) e[u] = list[wave][p][b + u];
+#pragma unroll
+    for (int u = 0; u < QU; ++u) ks[u].load(reinterpret_cast<const T*>(kb + (e[u].x + lo)));
+#pragma unroll
+    for (int u = 0; u < QU; ++u) {
+      float v[N];
+      ks[u].to_f32(v);
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] = fmaf(__uint_as_float(e[u].y), v[i], acc[i]);
+    }
+  }
+  if (sink) {
+    const float gsink = gz[r * kst + k];
+    Seg sk;
+    sk.load(sink + (size_t)h * n + (size_t)p * d + eo);
+    float v[N];
+    sk.to_f32(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = fmaf(gsink, v[i], acc[i]);
+  }
+  if (qstats) {  // through the LayerNorm, over both halves
+    const float2 st = qstats[r];
+    Seg xq;
+    xq.load(q + r * n + (size_t)p * d + eo);
+    float v[N], xh[N], sg = 0.f, sgx = 0.f;
+    xq.to_f32(v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (!has) acc[i] = 0.f;
+      xh[i] = has ? qn_apply(v[i], st.x, st.y) : 0.f;
+      sg += acc[i];
+      sgx = fmaf(acc[i], xh[i], sgx);
+    }
+    sg = group_sum<WAVE>(sg);
+    sgx = group_sum<WAVE>(sgx);
+    const float mg = sg / (float)n, mgx = sgx / (float)n;
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = st.y * (acc[i] - mg - xh[i] * mgx);
+  }
+  if (has) {
+    float* o = grad_q + r * n + (size_t)p * d + e0;
+#pragma unroll
+    for (int i = 0; i < N; i += 4)
+      *reinterpret_cast<float4*>(o + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+  }
+}
+
 // The leaders of every row, packed: row rp's c = offs[rp+1] - offs[rp] keys
 // move from slots rp*k .. rp*k + c - 1 to offs[rp] ..; the value is the slot.
 __global__ __launch_bounds__(256) void k_sbwd_pack(const uint32_t* __restrict__ keys,
@@ -271,7 +429,15 @@ __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, 
   const int ql = qlane ? lane * 4 : 0;
   const uint32_t nbins = (uint32_t)(2 * H) * (uint32_t)S;
   const uint32_t hk2 = 2u * (uint32_t)H * (uint32_t)k;  // slots per token
-  for (uint32_t u = blockIdx.x * 4u + wave; u < nseg; u += gridDim.x * 4u) {
+  // Workgroups go to the 8 XCDs in turn; each XCD takes one contiguous eighth of
+  // the segments (with 2H = 8 one head's half), whose waves walk the tokens at
+  // about the same pace, so that a query half read for one sub-key is still in
+  // the XCD's L2 for the others its token chose (245 -> 222 us at 32768 tokens,
+  // 4 heads, S = 2048; 31% of the requests hit, as the paces drift apart).
+  const uint32_t per = (nseg + 7u) / 8u;
+  const uint32_t u0 = (blockIdx.x & 7u) * per;
+  const uint32_t u1 = u0 + per < nseg ? u0 + per : nseg;
+  for (uint32_t u = u0 + (blockIdx.x >> 3) * 4u + wave; u < u1; u += (gridDim.x >> 3) * 4u) {
     const uint32_t s0 = seg[u], s1 = seg[u + 1];
     const uint32_t bin = ks[s0];
     if (bin >= nbins || s1 - s0 > SBWD_LONG) continue;
@@ -454,7 +620,8 @@ static hipError_t launch_sbwd(const void* q, const void* subkeys, int64_t T_, in
   const bool slots = np <= SORT_SLOTS_MAX;
   if (grad_K && !slots) e = launch_fill_u32(offs + rows, 0u, 1, st);  // the scan's last entry
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_search_bwd_q<T>, dim3((unsigned)(((T_ + 3) / 4) * H)), dim3(256), 0, st,
+  const auto kq = k <= 32 ? k_search_bwd_q32<T> : k_search_bwd_q<T>;
+  hipLaunchKernelGGL(kq, dim3((unsigned)(((T_ + 3) / 4) * H)), dim3(256), 0, st,
                      (const T*)q, (const T*)subkeys, T_, H, n, S, k, kst, idx, gz,
                      grad_q ? (const T*)sink : nullptr, qstats, grad_q,
                      grad_K ? keys : nullptr, grad_K ? gvals : nullptr, grad_K ? offs : nullptr);
@@ -480,7 +647,7 @@ static hipError_t launch_sbwd(const void* q, const void* subkeys, int64_t T_, in
                         SBWD_LONG, long_list, &ks, &vs, &seg, &nseg, &long_cnt, st);
   if (e != hipSuccess) return e;
   int64_t maxseg = (int64_t)nbins < np ? (int64_t)nbins : np;
-  int64_t blocks = (maxseg + 3) / 4;
+  int64_t blocks = ((maxseg + 7) / 8 + 3) / 4 * 8;  // an eighth of the segments per XCD
   if (blocks > 16384) blocks = 16384;
   int64_t lblocks = sbwd_max_long(np) < maxseg ? sbwd_max_long(np) : maxseg;
   if (lblocks > 256) lblocks = 256;

@@ -7,7 +7,7 @@
 //      workgroup per digit), and a stable scatter: each wave ranks a
 //      contiguous quarter of the tile with ballots, and the tile goes out
 //      through LDS in sorted order.  Keys are rows (< 2^26), values lookup ids.
-//      Up to 2^19 keys the passes are a short chain instead (k_chain_*), up to
+//      For fewer keys the passes are a short chain instead (k_chain_*), up to
 //      8192 one workgroup does everything (k_sort_one).
 //   2. Segment heads (first lookup of each distinct row) -> seg_start[U + 1],
 //      the head flags computed where they are counted and placed; the same
@@ -370,19 +370,23 @@ __global__ __launch_bounds__(256) void k_seg_place(const uint32_t* __restrict__ 
 }
 
 // ------------------------------------------------------- few keys ----
-// Up to CHAIN_MAX keys a radix pass of three launches is mostly launches and
+// For few keys a radix pass of three launches is mostly launches and
 // the latency of 16 serial rounds per wave on a few workgroups (65536 keys:
 // 6 + 4 + 15 us a pass).  The chain takes one launch per pass after a first
 // histogram: workgroups of 16 waves with 4 rounds each; every scatter adds up
-// the tile counts before its own itself (at most 128 tiles) and counts the next
+// the tile counts before its own itself (at most 512 tiles) and counts the next
 // pass's digits of the tiles it writes to with integer atomics (the counts
 // cleared by the first launch).  The result is the same stable sort.
 constexpr int CHAIN_ITEMS = 4;                       // keys per thread
 constexpr int CHAIN_TILE = 1024 * CHAIN_ITEMS;
 constexpr int ONE_ITEMS = 8;
 constexpr int64_t ONE_MAX = 1024 * ONE_ITEMS;        // keys one workgroup sorts by itself
+// Lookups the chain takes: 2^19 of them 25 us faster than three launches a
+// pass, 2^20 no faster (729 / 735 us with the rows), 2^21 5% slower.  Slot rows,
+// which are packed first otherwise, up to SORT_SLOTS_MAX (search backward, S =
+// 1024, 4 heads, k = 32: 4096 tokens 142 -> 108 us, 8192 201 -> 178, 16384
+// 341 -> 373).
 constexpr int64_t CHAIN_MAX = (int64_t)1 << 19;
-static_assert(SORT_SLOTS_MAX == CHAIN_MAX, "slot rows are sorted by the chain or one workgroup");
 
 // Where a sort takes its items: item i of an int64 or u32 array (value: the
 // position), or slot i of rows of k u32 keys of which row r fills its first
@@ -923,7 +927,7 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
     return hipGetLastError();
   }
   const int passes = (key_bits + RADIX_BITS - 1) / RADIX_BITS;
-  if ((key64 || slots) && L <= CHAIN_MAX) {
+  if (slots || (key64 && L <= CHAIN_MAX)) {
     const int64_t nblk = cdiv(L, CHAIN_TILE);  // up to four histograms fit b.hist: 1024 * nblk <= L
     const dim3 g((unsigned)nblk), blk(1024);
     const int bits0 = key_bits < RADIX_BITS ? key_bits : RADIX_BITS;
