@@ -36,7 +36,13 @@ constexpr int SORT_ITEMS = 16;                 // keys per thread per tile
 constexpr int SORT_TILE = 256 * SORT_ITEMS;    // keys per workgroup tile
 constexpr int SCAN_ITEMS = 8;
 constexpr uint32_t LONG_SEG = 1024;  // lookups of a row beyond which it is split
-constexpr uint32_t LONG_CHUNK = 1024;  // lookups of a long row per workgroup
+constexpr uint32_t LONG_CHUNK = 1024;  // lookups of a long row per workgroup, at most
+// Fewer where the long rows are few: their lookups are spread over LONG_WGS
+// workgroups.  A chunk is a serial chain of dy reads in each wave, so the sink
+// rows of 3 heads (9003 lookups, D = 640) took 70 us as 9 chunks of 1024 and
+// 13 us as 72 of 128.
+constexpr uint32_t LONG_WGS = 256;
+constexpr uint32_t LONG_CHUNK_MIN = 128;
 constexpr int LONG_WAVES = 8;        // waves of the workgroup that takes a chunk
 constexpr int SCAN_TILE = 256 * SCAN_ITEMS;
 constexpr int64_t SEG_TILES_MAX = 8192;  // tiles whose counts k_seg_place adds up itself
@@ -878,7 +884,7 @@ static SortedWs carve(void* ws, int64_t L) {
   w.hist = take(4 * (size_t)scan_n);
   w.sums = take(4 * (size_t)(cdiv(scan_n, SCAN_TILE) + 1));
   w.seg = take(4 * (size_t)(L + 1));
-  w.misc = take(256);  // [0] segments, [1] long rows listed
+  w.misc = take(256);  // [0] segments, [1] long rows listed, [2] their chunk length, [3] items
   w.long_list = take(4 * (size_t)max_long(L));
   w.totals = take(4 * (size_t)RADIX);  // a radix pass's count per digit
   w.long_base = take(4 * (size_t)(max_long(L) + 1));  // first chunk of each listed long row
@@ -1025,33 +1031,57 @@ hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStre
 }
 
 // Rows listed with the segments (more than LONG_SEG lookups) are cut into chunks
-// of LONG_CHUNK consecutive lookups (in lookup order), and every chunk of
+// of consecutive lookups (in lookup order), and every chunk of
 // every listed row is summed by a workgroup of its own, so a row chosen by a
 // large share of the tokens is spread over many CUs:
-//   k_long_bases    (one workgroup) the first chunk number of each listed row
+//   k_long_bases    (one workgroup) the chunk length, from the listed rows'
+//                   lookups, and the first chunk number of each listed row
 //                   (an exclusive scan of the chunk counts, in list order),
 //   k_bag_bwd_long  (persistent grid over the chunks) the chunk's lane groups
 //                   take contiguous runs of its lookups, write their grad_w and
 //                   sum w * dy into partial rows in LDS, added in group order
 //                   into the chunk's partial row in the workspace,
 //   k_long_reduce   (one workgroup per listed row) adds the row's partial rows
-//                   in chunk order to the old gradient row (dense) or writes
-//                   their sum as the row's gradient (sparse).
+//                   to the old gradient row (dense) or writes their sum as the
+//                   row's gradient (sparse): each of the workgroup's thread
+//                   groups a contiguous run of them in chunk order, the runs in
+//                   order.
 // The list's order varies from run to run, but a row's value depends only on
-// its own chunks, summed in chunk order: bitwise deterministic.
+// its own chunks and their length, which depends only on the lengths of the
+// listed rows: bitwise deterministic.
+// chunk_cap: L / LONG_CHUNK.  With n lookups in the listed rows there are at most
+// n / c whole chunks of c and one more per row; n / c <= chunk_cap both for
+// c >= n / chunk_cap and for c = LONG_CHUNK, which long_partial_bytes holds.
 __global__ __launch_bounds__(256) void k_long_bases(const uint32_t* __restrict__ seg_start,
                                                     const uint32_t* __restrict__ long_list,
                                                     const uint32_t* __restrict__ long_cnt,
+                                                    uint32_t chunk_cap,
+                                                    uint32_t* __restrict__ chunk_out,
                                                     uint32_t* __restrict__ long_base) {
   __shared__ uint32_t wsum[4];
   const uint32_t nlong = *long_cnt;
+  if (nlong == 0) {
+    if (threadIdx.x == 0) long_base[0] = 0;
+    return;
+  }
+  uint32_t mine = 0, lookups;
+  for (uint32_t i = threadIdx.x; i < nlong; i += 256) {
+    const uint32_t u = long_list[i];
+    mine += seg_start[u + 1] - seg_start[u];
+  }
+  block_exclusive_scan(mine, wsum, lookups);
+  const uint32_t parts = chunk_cap < LONG_WGS ? chunk_cap : LONG_WGS;  // a listed row: at least 1
+  uint32_t chunk = (lookups + parts - 1) / parts;
+  if (chunk < LONG_CHUNK_MIN) chunk = LONG_CHUNK_MIN;
+  if (chunk > LONG_CHUNK) chunk = LONG_CHUNK;
+  if (threadIdx.x == 0) *chunk_out = chunk;
   uint32_t carry = 0;
   for (uint32_t i0 = 0; i0 < nlong; i0 += 256) {
     const uint32_t i = i0 + threadIdx.x;
     uint32_t nch = 0;
     if (i < nlong) {
       const uint32_t u = long_list[i];
-      nch = (seg_start[u + 1] - seg_start[u] + LONG_CHUNK - 1) / LONG_CHUNK;
+      nch = (seg_start[u + 1] - seg_start[u] + chunk - 1) / chunk;
     }
     uint32_t total;
     const uint32_t before = block_exclusive_scan(nch, wsum, total);
@@ -1066,8 +1096,9 @@ __global__ __launch_bounds__(64 * LONG_WAVES) void k_bag_bwd_long(
     const V* __restrict__ dy, const V* __restrict__ values, int D, const float* __restrict__ w,
     int bag, const uint32_t* __restrict__ rows_sorted, const uint32_t* __restrict__ lookups,
     const uint32_t* __restrict__ seg_start, const uint32_t* __restrict__ long_list,
-    const uint32_t* __restrict__ long_cnt, const uint32_t* __restrict__ long_base,
-    float* __restrict__ part, float* __restrict__ grad_w) {
+    const uint32_t* __restrict__ long_cnt, const uint32_t* __restrict__ chunk_p,
+    const uint32_t* __restrict__ long_base, float* __restrict__ part,
+    float* __restrict__ grad_w) {
   using Q = Quad<V>;
   constexpr int G = WAVE / CL;
   constexpr int PB = RowsBatch<NQ, CL>::value;
@@ -1083,6 +1114,7 @@ __global__ __launch_bounds__(64 * LONG_WAVES) void k_bag_bwd_long(
   for (int m = 0; m < NQ; ++m) ok[m] = mine && (m * CL + cl) < nquad;
   const uint32_t nlong = *long_cnt;
   const uint32_t nchunk = long_base[nlong];
+  const uint32_t chunk = *chunk_p;
   for (uint32_t g = blockIdx.x; g < nchunk; g += gridDim.x) {
     // the listed row holding chunk g: long_base is ascending
     uint32_t lo = 0, hi = nlong;  // long_base[lo] <= g < long_base[hi]
@@ -1094,8 +1126,8 @@ __global__ __launch_bounds__(64 * LONG_WAVES) void k_bag_bwd_long(
     const uint32_t u = long_list[lo];
     const uint32_t c = g - long_base[lo];
     const uint32_t s_end = seg_start[u + 1];
-    const uint32_t c0 = seg_start[u] + c * LONG_CHUNK;
-    const uint32_t c1 = c0 + LONG_CHUNK < s_end ? c0 + LONG_CHUNK : s_end;
+    const uint32_t c0 = seg_start[u] + c * chunk;
+    const uint32_t c1 = c0 + chunk < s_end ? c0 + chunk : s_end;
     const int64_t row = (int64_t)rows_sorted[c0];
     const uint32_t len = c1 - c0;
     const uint32_t per = (len + (uint32_t)ng - 1) / (uint32_t)ng;
@@ -1167,34 +1199,57 @@ __global__ __launch_bounds__(64 * LONG_WAVES) void k_bag_bwd_long(
   }
 }
 
+constexpr int REDUCE_THREADS = 1024;
 template <bool SPARSE>
-__global__ __launch_bounds__(256) void k_long_reduce(int D, const uint32_t* __restrict__ rows_sorted,
-                                                     const uint32_t* __restrict__ seg_start,
-                                                     const uint32_t* __restrict__ long_list,
-                                                     const uint32_t* __restrict__ long_cnt,
-                                                     const uint32_t* __restrict__ long_base,
-                                                     const float* __restrict__ part,
-                                                     float* __restrict__ grad_values,
-                                                     int64_t* __restrict__ rows_out,
-                                                     float* __restrict__ grad_rows_out) {
+__global__ __launch_bounds__(REDUCE_THREADS) void k_long_reduce(
+    int D, const uint32_t* __restrict__ rows_sorted, const uint32_t* __restrict__ seg_start,
+    const uint32_t* __restrict__ long_list, const uint32_t* __restrict__ long_cnt,
+    const uint32_t* __restrict__ long_base, const float* __restrict__ part,
+    float* __restrict__ grad_values, int64_t* __restrict__ rows_out,
+    float* __restrict__ grad_rows_out) {
+  constexpr int U = 8;  // partial rows in flight per thread
+  __shared__ float4 run[REDUCE_THREADS];
   const uint32_t nlong = *long_cnt;
-  const int nquad = D / 4;
+  const int nquad = D / 4;  // at most 1024
   const bool dense = !SPARSE && grad_values != nullptr;
+  const int ng = REDUCE_THREADS / nquad;
+  const int grp = (int)threadIdx.x / nquad, qd = (int)threadIdx.x - grp * nquad;
   for (uint32_t i = blockIdx.x; i < nlong; i += gridDim.x) {
     const uint32_t u = long_list[i];
     const int64_t row = (int64_t)rows_sorted[seg_start[u]];
-    const uint32_t b0 = long_base[i], b1 = long_base[i + 1];
-    for (int qd = threadIdx.x; qd < nquad; qd += blockDim.x) {
+    const uint32_t b0 = long_base[i], cnt = long_base[i + 1] - b0;
+    const uint32_t per = (cnt + (uint32_t)ng - 1) / (uint32_t)ng;
+    if (grp < ng) {
+      const uint32_t a = (uint32_t)grp * per < cnt ? (uint32_t)grp * per : cnt;
+      const uint32_t z = a + per < cnt ? a + per : cnt;
+      const float* src = part + (size_t)b0 * D + (size_t)qd * 4;
       float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (dense) tot = *reinterpret_cast<const float4*>(grad_values + row * D + (size_t)qd * 4);
-      for (uint32_t g = b0; g < b1; ++g) {
-        const float4 pv = *reinterpret_cast<const float4*>(part + (size_t)g * D + (size_t)qd * 4);
+      for (uint32_t g = a; g < z; g += U) {
+        float4 pv[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+          pv[j] = g + j < z ? *reinterpret_cast<const float4*>(src + (size_t)(g + j) * D)
+                            : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          tot.x += pv[j].x; tot.y += pv[j].y; tot.z += pv[j].z; tot.w += pv[j].w;
+        }
+      }
+      run[threadIdx.x] = tot;
+    }
+    __syncthreads();
+    if (grp == 0 && (SPARSE || dense)) {
+      float* dst = (SPARSE ? grad_rows_out + (size_t)u * D : grad_values + row * D) + (size_t)qd * 4;
+      float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (dense) tot = *reinterpret_cast<const float4*>(dst);
+      for (int j = 0; j < ng; ++j) {
+        const float4 pv = run[j * nquad + qd];
         tot.x += pv.x; tot.y += pv.y; tot.z += pv.z; tot.w += pv.w;
       }
-      float* dst = SPARSE ? grad_rows_out + (size_t)u * D : grad_values + row * D;
-      if (SPARSE || dense) *reinterpret_cast<float4*>(dst + (size_t)qd * 4) = tot;
+      *reinterpret_cast<float4*>(dst) = tot;
     }
     if (SPARSE && threadIdx.x == 0) rows_out[u] = row;
+    __syncthreads();  // run is reused for the next row
   }
 }
 
@@ -1233,7 +1288,8 @@ hipError_t launch_bag_backward_sorted(bool bf16, const void* dy, const void* val
   if (rblocks > 512) rblocks = 512;
   const int ngrp_cap = 16384 / D;  // partial rows that fit 64 KiB
   hipLaunchKernelGGL(k_long_bases, dim3(1), dim3(256), 0, st, (const uint32_t*)b.seg,
-                     (const uint32_t*)b.long_list, (const uint32_t*)(b.misc + 1), b.long_base);
+                     (const uint32_t*)b.long_list, (const uint32_t*)(b.misc + 1),
+                     (uint32_t)(L / LONG_CHUNK), b.misc + 2, b.long_base);
   LaunchTimer lt("bag_backward_rows", st);
 #define PK_ROWS_ONE(VT, NQ, CL, SP)                                                                \
   {                                                                                                \
@@ -1244,8 +1300,8 @@ hipError_t launch_bag_backward_sorted(bool bf16, const void* dy, const void* val
     hipLaunchKernelGGL((k_bag_bwd_long<VT, NQ, CL>), dim3((unsigned)lblocks),                      \
                        dim3(64 * LONG_WAVES), (size_t)ng * D * sizeof(float), st, (const VT*)dy,   \
                        (const VT*)values, D, w, bag, ks, vs, b.seg, b.long_list, b.misc + 1,       \
-                       b.long_base, part, grad_w);                                                \
-    hipLaunchKernelGGL((k_long_reduce<SP>), dim3((unsigned)rblocks), dim3(256), 0, st, D, ks,      \
+                       b.misc + 2, b.long_base, part, grad_w);                                    \
+    hipLaunchKernelGGL((k_long_reduce<SP>), dim3((unsigned)rblocks), dim3(REDUCE_THREADS), 0, st, D, ks,      \
                        b.seg, b.long_list, b.misc + 1, b.long_base, part, grad_values, rows_out,   \
                        grad_rows_out);                                                             \
   }
