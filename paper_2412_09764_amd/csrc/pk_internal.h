@@ -82,14 +82,10 @@ struct SortSrc {
   const uint32_t* counts;
   int k;
 };
-constexpr int64_t SORT_SLOTS_MAX = (int64_t)1 << 21;  // slots a sort takes as they are
-void sort_u32_inputs(void* ws, int64_t Lmax, uint32_t** keys_in, uint32_t** vals_in);
-hipError_t sort_u32_segments(const SortSrc* slots, int64_t Lmax, const uint32_t* Ldev, int key_bits,
-                             void* ws, uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
-                             const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
-                             const uint32_t** nlong, hipStream_t st);
-size_t scan_scratch_u32(int64_t n);
-hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStream_t st);
+hipError_t sort_slots_segments(const SortSrc& slots, int64_t nslots, int key_bits, void* ws,
+                               uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
+                               const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
+                               const uint32_t** nlong, hipStream_t st);
 // qstats (nullable): the queries were normalised in the forward (their
 // (mean, rstd) from launch_qnorm); grad_q is then taken through the
 // normalisation and grad_K uses the normalised queries as scored.

@@ -15,10 +15,10 @@
 // atomics, in global memory or in LDS, serialise on them.  Instead the same
 // wave emits one (head, half, sub-key) sort key per group leader, with the
 // group's gradient sum, at the front of its (token, head, half) row of k
-// slots, and counts them; the library's stable radix sort orders the leaders by
-// key (for many rows an exclusive scan of the counts first places them
-// contiguously, in slot order).  One wave per segment then sums gsum * q over the
-// segment's tokens (in token order; each token's query half is read once) and
+// slots, and counts them; the leaders are then brought into sub-key order, equal
+// ones in token order: by a counting sort over the sub-keys (k_bin_*), or, for
+// few leaders, by the library's radix sort.  One wave per sub-key sums gsum * q over
+// its tokens (in token order; each token's query half is read once) and
 // adds the sum into the sub-key row with one plain read-modify-write: no
 // atomics, bitwise deterministic.  A segment longer than 2048 pairs (a
 // sub-key that thousands of tokens chose) goes to a workgroup of 16 waves
@@ -340,40 +340,209 @@ __global__ __launch_bounds__(256) void k_search_bwd_q32(
   }
 }
 
-// The leaders of every row, packed: row rp's c = offs[rp+1] - offs[rp] keys
-// move from slots rp*k .. rp*k + c - 1 to offs[rp] ..; the value is the slot.
-__global__ __launch_bounds__(256) void k_sbwd_pack(const uint32_t* __restrict__ keys,
-                                                   const uint32_t* __restrict__ offs, int64_t rows,
-                                                   int k, uint32_t* __restrict__ keys_out,
-                                                   uint32_t* __restrict__ slot_out) {
-  const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (x >= rows * k) return;
-  const int64_t rp = x / k;
-  const uint32_t j = (uint32_t)(x - rp * k);
-  const uint32_t o = offs[rp];
-  if (j < offs[rp + 1] - o) {
-    keys_out[o + j] = keys[x];
-    slot_out[o + j] = (uint32_t)x;
+// Counting sort of the leaders by sub-key, each (head, half) for itself: its
+// leaders go to its own T * k places of the pair array, so only the S sub-keys
+// of one table are sorted over.  The leaders of one (token, head, half) row have
+// distinct sub-keys, so a wave that takes a run of tile_tok tokens row by row
+// ranks them with one returning LDS add per row, without ballots:
+//   k_bin_count    counts per (head, half, tile, sub-key),
+//   k_bin_scan     per sub-key an exclusive scan over the tiles, and its total,
+//   k_bin_scatter  the sub-keys' starts (a scan of the totals by every wave),
+//                  then (token, gradient sum) of each leader to its place; the
+//                  first tile's waves also list the sub-keys of more than
+//                  SBWD_LONG tokens.
+// The keys come straight from the slots, the sub-key sums read their pairs in
+// order.  At 32768 tokens, 4 heads, S = 2048, k = 32 (2.9M leaders) 22 + 9 + 65
+// us, the scatter's 8-byte writes to 2048 running places per table being most of
+// it (neither non-temporal reads nor reading a batch ahead changed that).  A scan
+// of the counts, a packing of the leaders, two radix passes and the marking of
+// segments in 13 launches took 157, and left the sums another gather (221 us
+// with it, 179 without).  Whole search backward 546 -> 454 us; training steps with
+// it: 16384 tokens 3240 -> 3175, 3001 tokens 480 -> 461, 512 tokens 389 -> 373.
+constexpr uint32_t SBWD_LONG = 2048;  // pairs of a sub-key beyond which k_sbwd_long sums them
+constexpr int BIN_U = 16;             // rows in flight per wave
+
+// f(token, lane's slot is filled, key, gradient sum) for the tile's rows in order.
+template <bool VALS, typename F>
+__device__ __forceinline__ void bin_rows(const uint32_t* __restrict__ keys,
+                                         const float* __restrict__ gvals,
+                                         const uint32_t* __restrict__ counts, int64_t t0, int64_t t1,
+                                         int H, int hp, int k, F f) {
+  const int lane = threadIdx.x;
+  const int HP = 2 * H;
+  const bool slot = lane < k;
+  for (int64_t tb = t0; tb < t1; tb += WAVE) {
+    const uint32_t c = tb + lane < t1 ? counts[(tb + lane) * HP + hp] : 0u;
+    const int nt = t1 - tb < WAVE ? (int)(t1 - tb) : WAVE;
+    for (int i = 0; i < nt; i += BIN_U) {
+      uint32_t key[BIN_U];
+      float g[BIN_U];
+#pragma unroll
+      for (int u = 0; u < BIN_U; ++u) {
+        const bool has = slot && i + u < nt;
+        const size_t x = has ? (size_t)((tb + i + u) * HP + hp) * k + lane : 0;
+        key[u] = has ? keys[x] : 0u;
+        g[u] = VALS && has ? gvals[x] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < BIN_U; ++u) {  // past nt the counts are 0 (i + u < 64)
+        const uint32_t cu = (uint32_t)__builtin_amdgcn_readlane((int)c, i + u);
+        f((uint32_t)(tb + i + u), (uint32_t)lane < cu, key[u], g[u]);
+      }
+    }
   }
 }
+
+__global__ __launch_bounds__(64) void k_bin_count(const uint32_t* __restrict__ keys,
+                                                  const uint32_t* __restrict__ counts, int64_t ntok,
+                                                  int H, int S, int k, int tile_tok,
+                                                  uint32_t* __restrict__ mat,
+                                                  uint32_t* __restrict__ long_cnt) {
+  extern __shared__ uint32_t cnt[];  // [S]
+  const int lane = threadIdx.x;
+  const int hp = (int)(blockIdx.x % (unsigned)(2 * H));
+  const int64_t tile = blockIdx.x / (unsigned)(2 * H);
+  if (blockIdx.x == 0 && lane == 0) *long_cnt = 0;
+  for (int b = lane; b < S; b += WAVE) cnt[b] = 0;
+  __syncthreads();
+  const int64_t t0 = tile * tile_tok, t1 = t0 + tile_tok < ntok ? t0 + tile_tok : ntok;
+  const uint32_t key0 = (uint32_t)hp * (uint32_t)S;
+  bin_rows<false>(keys, nullptr, counts, t0, t1, H, hp, k,
+                  [&](uint32_t, bool has, uint32_t key, float) {
+                    if (has) atomicAdd(&cnt[key - key0], 1u);
+                  });
+  __syncthreads();
+  uint32_t* out = mat + (size_t)blockIdx.x * S;  // [tile][head, half][sub-key]
+  for (int b = lane; b < S; b += WAVE) out[b] = cnt[b];
+}
+
+// 64 bins per workgroup, each by 16 threads with a run of the tiles each.
+__global__ __launch_bounds__(1024) void k_bin_scan(uint32_t* __restrict__ mat, int64_t nbins,
+                                                   int ntile, uint32_t* __restrict__ totals) {
+  constexpr int U = 8;
+  __shared__ uint32_t part[16][WAVE];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t bin = (int64_t)blockIdx.x * WAVE + lane;
+  const bool live = bin < nbins;
+  const int per = (ntile + 15) / 16;
+  const int a = grp * per < ntile ? grp * per : ntile;
+  const int z = a + per < ntile ? a + per : ntile;
+  uint32_t* m = mat + (live ? bin : 0);
+  uint32_t sum = 0;
+  for (int i = a; i < z; i += U) {
+    uint32_t v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = i + j < z ? m[(int64_t)(i + j) * nbins] : 0u;
+#pragma unroll
+    for (int j = 0; j < U; ++j) sum += v[j];
+  }
+  part[grp][lane] = sum;
+  __syncthreads();
+  uint32_t run = 0, all = 0;
+#pragma unroll
+  for (int g = 0; g < 16; ++g) {
+    const uint32_t v = part[g][lane];
+    run += g < grp ? v : 0u;
+    all += v;
+  }
+  if (!live) return;
+  if (grp == 0) totals[bin] = all;
+  for (int i = a; i < z; i += U) {
+    uint32_t v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = i + j < z ? m[(int64_t)(i + j) * nbins] : 0u;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (i + j < z) m[(int64_t)(i + j) * nbins] = run;
+      run += v[j];
+    }
+  }
+}
+
+__global__ __launch_bounds__(64) void k_bin_scatter(
+    const uint32_t* __restrict__ keys, const float* __restrict__ gvals,
+    const uint32_t* __restrict__ counts, int64_t ntok, int H, int S, int k, int tile_tok,
+    const uint32_t* __restrict__ mat, const uint32_t* __restrict__ totals,
+    uint32_t* __restrict__ starts, uint2* __restrict__ pairs, uint32_t* __restrict__ long_list,
+    uint32_t* __restrict__ long_cnt) {
+  extern __shared__ uint32_t cnt[];  // [S] the next place of each sub-key
+  const int lane = threadIdx.x;
+  const int hp = (int)(blockIdx.x % (unsigned)(2 * H));
+  const int64_t tile = blockIdx.x / (unsigned)(2 * H);
+  const uint32_t key0 = (uint32_t)hp * (uint32_t)S;
+  const uint32_t* pre = mat + (size_t)blockIdx.x * S;
+  uint32_t carry = (uint32_t)hp * (uint32_t)(ntok * k);  // the (head, half)'s own places
+#pragma unroll 4
+  for (int b0 = 0; b0 < S; b0 += 4 * WAVE) {
+    const int b = b0 + lane * 4;
+    uint32_t v[4], w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = b + i < S ? totals[key0 + b + i] : 0u;
+      w[i] = b + i < S ? pre[b + i] : 0u;
+    }
+    const uint32_t mine = v[0] + v[1] + v[2] + v[3];
+    uint32_t x = mine;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    uint32_t at = carry + x - mine;
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (b + i < S) {
+        cnt[b + i] = at + w[i];
+        if (tile == 0) {
+          starts[key0 + b + i] = at;
+          if (v[i] > SBWD_LONG) long_list[atomicAdd(long_cnt, 1u)] = key0 + (uint32_t)(b + i);
+        }
+      }
+      at += v[i];
+    }
+  }
+  __syncthreads();
+  const int64_t t0 = tile * tile_tok, t1 = t0 + tile_tok < ntok ? t0 + tile_tok : ntok;
+  bin_rows<true>(keys, gvals, counts, t0, t1, H, hp, k,
+                 [&](uint32_t t, bool has, uint32_t key, float g) {
+                   if (has) pairs[atomicAdd(&cnt[key - key0], 1u)] = make_uint2(t, __float_as_uint(g));
+                 });
+}
+
+// Where the sums find the sorted leaders: the counting sort's pairs with each
+// sub-key's start and number, or the radix sort's keys, slots and segments.
+struct SbwdPairs {
+  const uint2* pairs;
+  const uint32_t *starts, *totals;
+  const float* gvals;
+  const uint32_t *ks, *vs, *seg, *nseg;
+};
 
 // Adds gsum * (query half as scored) of the sorted pairs [a, z) of one
 // (head h, half) segment into acc, in pair order: the pairs are taken 64 at a
 // time and consumed QU at a time, with their query-quad loads issued
 // together; lane l owns elements 4l..4l+3 of the half (qh points at them).
-template <typename T, bool QN>
+template <typename T, bool QN, bool BINS>
 __device__ __forceinline__ void sbwd_sum_run(const T* qh, int H, int n, int h, uint32_t hk2,
                                              const float2* __restrict__ qstats,
-                                             const float* __restrict__ gvals,
-                                             const uint32_t* __restrict__ vs, uint32_t a,
-                                             uint32_t z, int lane, float* acc) {
+                                             const SbwdPairs& in, uint32_t a, uint32_t z,
+                                             int lane, float* acc) {
   constexpr int QU = PK_SBWD_QU;
   for (uint32_t b0 = a; b0 < z; b0 += 64) {
     const uint32_t e = b0 + lane;
     const bool ok = e < z;
-    const uint32_t x = ok ? vs[e] : 0u;
-    const uint32_t t = x / hk2;
-    const float gx = ok ? gvals[x] : 0.f;
+    uint32_t t;
+    float gx;
+    if constexpr (BINS) {
+      const uint2 pr = ok ? in.pairs[e] : uint2{0, 0};
+      t = pr.x;
+      gx = __uint_as_float(pr.y);
+    } else {
+      const uint32_t x = ok ? in.vs[e] : 0u;
+      t = x / hk2;
+      gx = ok ? in.gvals[x] : 0.f;
+    }
     float2 st = make_float2(0.f, 1.f);
     if constexpr (QN) st = qstats[(size_t)t * H + h];
     const uint32_t cnt = (z - b0) < 64u ? (z - b0) : 64u;
@@ -404,30 +573,39 @@ __device__ __forceinline__ void sbwd_sum_run(const T* qh, int H, int n, int h, u
 
 // A segment of more than SBWD_LONG pairs (a sub-key chosen by that many
 // tokens) is summed by k_sbwd_long instead of one wave.
-constexpr uint32_t SBWD_LONG = 2048;
 constexpr int SBWD_LWAVES = 16;
 static int64_t sbwd_max_long(int64_t np) { return np / SBWD_LONG + 1; }
+
+// Segment u: its sub-key (over all heads and halves) and its pairs [s0, s1).
+template <bool BINS>
+__device__ __forceinline__ uint32_t sbwd_segment(const SbwdPairs& in, uint32_t u, uint32_t& s0,
+                                                 uint32_t& s1) {
+  if constexpr (BINS) {
+    s0 = in.starts[u];
+    s1 = s0 + in.totals[u];
+    return u;
+  } else {
+    s0 = in.seg[u];
+    s1 = in.seg[u + 1];
+    return in.ks[s0];
+  }
+}
 
 // One wave per segment (grid-stride) of the sorted pairs; a segment is one
 // (head, half, sub-key) and holds at most one pair per token, in token order.
 // Lane l owns elements 4l..4l+3 of the d-element row (d <= 256).  The sum is
 // added into the sub-key row with one read-modify-write.
-template <typename T, bool QN>
+template <typename T, bool QN, bool BINS>
 __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, int H, int n,
                                                        int S, int k,
                                                        const float2* __restrict__ qstats,
-                                                       const float* __restrict__ gvals,
-                                                       const uint32_t* __restrict__ ks,
-                                                       const uint32_t* __restrict__ vs,
-                                                       const uint32_t* __restrict__ seg,
-                                                       const uint32_t* __restrict__ nseg_p,
-                                                       float* __restrict__ grad_K) {
+                                                       SbwdPairs in, float* __restrict__ grad_K) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t nseg = *nseg_p;
+  const uint32_t nbins = (uint32_t)(2 * H) * (uint32_t)S;
+  const uint32_t nseg = BINS ? nbins : *in.nseg;
   const int d = n >> 1;
   const bool qlane = lane * 4 < d;
   const int ql = qlane ? lane * 4 : 0;
-  const uint32_t nbins = (uint32_t)(2 * H) * (uint32_t)S;
   const uint32_t hk2 = 2u * (uint32_t)H * (uint32_t)k;  // slots per token
   // Workgroups go to the 8 XCDs in turn; each XCD takes one contiguous eighth of
   // the segments (with 2H = 8 one head's half), whose waves walk the tokens at
@@ -438,14 +616,14 @@ __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, 
   const uint32_t u0 = (blockIdx.x & 7u) * per;
   const uint32_t u1 = u0 + per < nseg ? u0 + per : nseg;
   for (uint32_t u = u0 + (blockIdx.x >> 3) * 4u + wave; u < u1; u += (gridDim.x >> 3) * 4u) {
-    const uint32_t s0 = seg[u], s1 = seg[u + 1];
-    const uint32_t bin = ks[s0];
-    if (bin >= nbins || s1 - s0 > SBWD_LONG) continue;
+    uint32_t s0, s1;
+    const uint32_t bin = sbwd_segment<BINS>(in, u, s0, s1);
+    if (bin >= nbins || s0 == s1 || s1 - s0 > SBWD_LONG) continue;
     const int hp = (int)(bin / (uint32_t)S);
     const int h = hp >> 1, p = hp & 1;
     const T* qh = q + (size_t)h * n + (size_t)p * d + ql;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    sbwd_sum_run<T, QN>(qh, H, n, h, hk2, qstats, gvals, vs, s0, s1, lane, acc);
+    sbwd_sum_run<T, QN, BINS>(qh, H, n, h, hk2, qstats, in, s0, s1, lane, acc);
     if (qlane) {
       float4* dst = reinterpret_cast<float4*>(grad_K + (size_t)bin * d + ql);
       float4 o = *dst;
@@ -459,12 +637,10 @@ __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, 
 // segment at a time: wave w sums the w-th contiguous run of the segment's
 // pairs (in pair order) into a partial row; the partial rows meet in LDS and
 // are added, in wave order, to the sub-key row with one read-modify-write.
-template <typename T, bool QN>
+template <typename T, bool QN, bool BINS>
 __global__ __launch_bounds__(64 * SBWD_LWAVES) void k_sbwd_long(
     const T* __restrict__ q, int H, int n, int S, int k, const float2* __restrict__ qstats,
-    const float* __restrict__ gvals, const uint32_t* __restrict__ ks,
-    const uint32_t* __restrict__ vs, const uint32_t* __restrict__ seg,
-    const uint32_t* __restrict__ long_list, const uint32_t* __restrict__ long_cnt,
+    SbwdPairs in, const uint32_t* __restrict__ long_list, const uint32_t* __restrict__ long_cnt,
     float* __restrict__ grad_K) {
   __shared__ float part[SBWD_LWAVES][256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -475,9 +651,8 @@ __global__ __launch_bounds__(64 * SBWD_LWAVES) void k_sbwd_long(
   const uint32_t hk2 = 2u * (uint32_t)H * (uint32_t)k;
   const uint32_t nlong = *long_cnt;
   for (uint32_t it = blockIdx.x; it < nlong; it += gridDim.x) {
-    const uint32_t u = long_list[it];
-    const uint32_t s0 = seg[u], s1 = seg[u + 1];
-    const uint32_t bin = ks[s0];
+    uint32_t s0, s1;
+    const uint32_t bin = sbwd_segment<BINS>(in, long_list[it], s0, s1);
     if (bin >= nbins) continue;  // the same for every wave of the workgroup
     const int hp = (int)(bin / (uint32_t)S);
     const int h = hp >> 1, p = hp & 1;
@@ -488,7 +663,7 @@ __global__ __launch_bounds__(64 * SBWD_LWAVES) void k_sbwd_long(
     a = s0 + (a < len ? a : len);
     z = s0 + (z < len ? z : len);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    sbwd_sum_run<T, QN>(qh, H, n, h, hk2, qstats, gvals, vs, a, z, lane, acc);
+    sbwd_sum_run<T, QN, BINS>(qh, H, n, h, hk2, qstats, in, a, z, lane, acc);
     if (qlane) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) part[wave][ql + i] = acc[i];
@@ -568,16 +743,39 @@ __global__ __launch_bounds__(256) void k_sink_reduce(const float* __restrict__ p
   grad_sink[e] += s;
 }
 
-// Workspace: keys and group sums per slot (2*T*H*k each), the row counts
-// (scanned in place into offsets, plus the total), the scan's partials, the
-// list of long segments, then the sort of up to 2*T*H*k pairs.
+// Workspace: keys and group sums per slot (2*T*H*k each), the row counts, a
+// spare part (a query for its size gives the same as ever), the list of long
+// segments, then the sort of up to 2*T*H*k leaders: the radix sort's, or the
+// counting sort's pairs (8 bytes each), tile counts, totals and starts.
 static size_t a256(size_t x) { return (x + 255) / 256 * 256; }
+static size_t sbwd_spare(int64_t rows) { return a256((size_t)((rows + 2048) / 2048 + 1) * 4); }
 size_t search_backward_ws_bytes(int64_t T, int H, int k) {
   const int64_t rows = 2 * T * H;
   const int64_t np = rows * k;
-  return 2 * a256((size_t)np * 4) + a256((size_t)(rows + 2) * 4) +
-         a256(scan_scratch_u32(rows + 1) * 4) + a256((size_t)sbwd_max_long(np) * 4) +
-         sorted_workspace_bytes(np);
+  return 2 * a256((size_t)np * 4) + a256((size_t)(rows + 2) * 4) + sbwd_spare(rows) +
+         a256((size_t)sbwd_max_long(np) * 4) + sorted_workspace_bytes(np);
+}
+
+// Tokens per wave of the counting sort, 0 where the radix sort is taken.  A wave's
+// rows are a serial chain, so a tile is small, but it writes and twice reads S
+// counts, so it has at least S / 2 slots, and there are at most about 2048 waves
+// (whole search backward, us, at 16 / 32 / 64 / 128 / 256 tokens: 512 tokens S 512 28 /
+// 31 / 37 / 50 / 77; 4096 tokens S 1024 68 / 65 / 68 / 81 / 107; 16384 tokens
+// 235 / 217 / 205 / 207 / 228; 32768 tokens S 2048 - / 468 / 447 / 453 / 465).  Up
+// to 8192 slots one workgroup sorts them all in one launch instead of three.
+// The counts, totals and starts have to fit the radix sort's share of the
+// workspace (sorted_workspace_bytes holds at least 6 words per slot, the pairs
+// take 2), which larger tiles give for T * k >= S; below that the chained
+// radix sort is taken.
+static int bin_tile_tokens(int64_t T, int H, int S, int k) {
+  const int64_t np = 2 * T * H * k;
+  if (np <= 8192) return 0;
+  int tile = 16;
+  while (tile * k < S / 2) tile *= 2;
+  while (2 * H * (T / tile) > 2048) tile *= 2;
+  while (tile < T && ((T + tile - 1) / tile + 2) * 2 * H * S + 192 > 4 * np) tile *= 2;
+  const int64_t ntile = (T + tile - 1) / tile;
+  return (ntile + 2) * 2 * H * S + 192 <= 4 * np ? tile : 0;
 }
 
 template <typename T>
@@ -607,62 +805,73 @@ static hipError_t launch_sbwd(const void* q, const void* subkeys, int64_t T_, in
   p += a256((size_t)np * 4);
   float* gvals = reinterpret_cast<float*>(p);
   p += a256((size_t)np * 4);
-  uint32_t* offs = reinterpret_cast<uint32_t*>(p);  // the row counts, scanned: rows + 1
+  uint32_t* counts = reinterpret_cast<uint32_t*>(p);  // leaders per row
   p += a256((size_t)(rows + 2) * 4);
-  uint32_t* sums = reinterpret_cast<uint32_t*>(p);
-  p += a256(scan_scratch_u32(rows + 1) * 4);
+  void* ws_spare = p;
+  p += sbwd_spare(rows);
   uint32_t* long_list = reinterpret_cast<uint32_t*>(p);
   p += a256((size_t)sbwd_max_long(np) * 4);
   void* sort_ws = p;
-  // Up to SORT_SLOTS_MAX slots are sorted as they lie, the unfilled ones
-  // dropped by the first pass: no scan and no pack (512 tokens, 4 heads,
-  // k = 32: from 18 launches to 8).  More are packed first.
-  const bool slots = np <= SORT_SLOTS_MAX;
-  if (grad_K && !slots) e = launch_fill_u32(offs + rows, 0u, 1, st);  // the scan's last entry
-  if (e != hipSuccess) return e;
   const auto kq = k <= 32 ? k_search_bwd_q32<T> : k_search_bwd_q<T>;
   hipLaunchKernelGGL(kq, dim3((unsigned)(((T_ + 3) / 4) * H)), dim3(256), 0, st,
                      (const T*)q, (const T*)subkeys, T_, H, n, S, k, kst, idx, gz,
                      grad_q ? (const T*)sink : nullptr, qstats, grad_q,
-                     grad_K ? keys : nullptr, grad_K ? gvals : nullptr, grad_K ? offs : nullptr);
+                     grad_K ? keys : nullptr, grad_K ? gvals : nullptr, grad_K ? counts : nullptr);
   e = hipGetLastError();
   if (e != hipSuccess || !grad_K) return e;
-  if (!slots) {
-    // counts -> offsets; offs[rows] = number of leaders
-    e = scan_exclusive_u32(offs, rows + 1, sums, st);
-    if (e != hipSuccess) return e;
-    uint32_t *kin, *vin;
-    sort_u32_inputs(sort_ws, np, &kin, &vin);
-    hipLaunchKernelGGL(k_sbwd_pack, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, keys, offs,
-                       rows, k, kin, vin);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   const uint32_t nbins = (uint32_t)(2 * H) * (uint32_t)S;
-  int key_bits = 1;
-  while (key_bits < 32 && (uint64_t(1) << key_bits) < nbins) ++key_bits;
-  const uint32_t *ks, *vs, *seg, *nseg, *long_cnt;
-  const SortSrc src{keys, offs, k};
-  e = sort_u32_segments(slots ? &src : nullptr, np, slots ? nullptr : offs + rows, key_bits, sort_ws,
-                        SBWD_LONG, long_list, &ks, &vs, &seg, &nseg, &long_cnt, st);
+  const int tile = bin_tile_tokens(T_, H, S, k);
+  SbwdPairs in{};
+  const uint32_t* long_cnt;
+  if (tile > 0) {
+    const int64_t ntile = (T_ + tile - 1) / tile;
+    uint2* pairs = reinterpret_cast<uint2*>(p);
+    p += a256((size_t)np * 8);
+    uint32_t* mat = reinterpret_cast<uint32_t*>(p);
+    p += a256((size_t)ntile * nbins * 4);
+    uint32_t* totals = reinterpret_cast<uint32_t*>(p);
+    p += a256((size_t)nbins * 4);
+    uint32_t* starts = reinterpret_cast<uint32_t*>(p);
+    uint32_t* lcnt = reinterpret_cast<uint32_t*>(ws_spare);
+    const dim3 g((unsigned)(ntile * 2 * H));
+    const size_t lds = (size_t)S * 4;
+    hipLaunchKernelGGL(k_bin_count, g, dim3(WAVE), lds, st, keys, counts, T_, H, S, k, tile, mat, lcnt);
+    hipLaunchKernelGGL(k_bin_scan, dim3((nbins + WAVE - 1) / WAVE), dim3(1024), 0, st, mat,
+                       (int64_t)nbins, (int)ntile, totals);
+    hipLaunchKernelGGL(k_bin_scatter, g, dim3(WAVE), lds, st, keys, gvals, counts, T_, H, S, k, tile,
+                       mat, totals, starts, pairs, long_list, lcnt);
+    e = hipGetLastError();
+    in.pairs = pairs;
+    in.starts = starts;
+    in.totals = totals;
+    long_cnt = lcnt;
+  } else {
+    int key_bits = 1;
+    while (key_bits < 32 && (uint64_t(1) << key_bits) < nbins) ++key_bits;
+    in.gvals = gvals;
+    e = sort_slots_segments(SortSrc{keys, counts, k}, np, key_bits, sort_ws, SBWD_LONG, long_list,
+                            &in.ks, &in.vs, &in.seg, &in.nseg, &long_cnt, st);
+  }
   if (e != hipSuccess) return e;
   int64_t maxseg = (int64_t)nbins < np ? (int64_t)nbins : np;
+  if (tile > 0) maxseg = nbins;
   int64_t blocks = ((maxseg + 7) / 8 + 3) / 4 * 8;  // an eighth of the segments per XCD
   if (blocks > 16384) blocks = 16384;
   int64_t lblocks = sbwd_max_long(np) < maxseg ? sbwd_max_long(np) : maxseg;
   if (lblocks > 256) lblocks = 256;
-  if (qstats) {
-    hipLaunchKernelGGL((k_sbwd_segments<T, true>), dim3((unsigned)blocks), dim3(256), 0, st,
-                       (const T*)q, H, n, S, k, qstats, gvals, ks, vs, seg, nseg, grad_K);
-    hipLaunchKernelGGL((k_sbwd_long<T, true>), dim3((unsigned)lblocks), dim3(64 * SBWD_LWAVES), 0,
-                       st, (const T*)q, H, n, S, k, qstats, gvals, ks, vs, seg,
-                       (const uint32_t*)long_list, (const uint32_t*)long_cnt, grad_K);
+  auto sums = [&](auto seg_kernel, auto long_kernel) {
+    hipLaunchKernelGGL(seg_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const T*)q, H, n, S, k,
+                       qstats, in, grad_K);
+    hipLaunchKernelGGL(long_kernel, dim3((unsigned)lblocks), dim3(64 * SBWD_LWAVES), 0, st,
+                       (const T*)q, H, n, S, k, qstats, in, (const uint32_t*)long_list, long_cnt,
+                       grad_K);
+  };
+  if (tile > 0) {
+    if (qstats) sums(k_sbwd_segments<T, true, true>, k_sbwd_long<T, true, true>);
+    else sums(k_sbwd_segments<T, false, true>, k_sbwd_long<T, false, true>);
   } else {
-    hipLaunchKernelGGL((k_sbwd_segments<T, false>), dim3((unsigned)blocks), dim3(256), 0, st,
-                       (const T*)q, H, n, S, k, qstats, gvals, ks, vs, seg, nseg, grad_K);
-    hipLaunchKernelGGL((k_sbwd_long<T, false>), dim3((unsigned)lblocks), dim3(64 * SBWD_LWAVES),
-                       0, st, (const T*)q, H, n, S, k, qstats, gvals, ks, vs, seg,
-                       (const uint32_t*)long_list, (const uint32_t*)long_cnt, grad_K);
+    if (qstats) sums(k_sbwd_segments<T, true, false>, k_sbwd_long<T, true, false>);
+    else sums(k_sbwd_segments<T, false, false>, k_sbwd_long<T, false, false>);
   }
   return hipGetLastError();
 }

@@ -51,7 +51,6 @@ static inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------------ scan ----
-// Exclusive prefix sum of u32, any length, in three launches.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t x = v;
@@ -67,19 +66,6 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* w
   total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
   __syncthreads();
   return before + x - v;
-}
-
-__global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* __restrict__ in, int64_t n,
-                                                     uint32_t* __restrict__ sums) {
-  __shared__ uint32_t wsum[4];
-  const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-  uint32_t s = 0;
-#pragma unroll
-  for (int i = 0; i < SCAN_ITEMS; ++i)
-    if (base + i < n) s += in[base + i];
-  uint32_t total;
-  block_exclusive_scan(s, wsum, total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
 // Single workgroup: exclusive scan of the tile sums, in place, any count.
@@ -104,36 +90,6 @@ __global__ __launch_bounds__(256) void k_scan_top(uint32_t* __restrict__ sums, i
     }
     carry += total;
   }
-}
-
-__global__ __launch_bounds__(256) void k_scan_down(const uint32_t* __restrict__ in,
-                                                   uint32_t* __restrict__ out, int64_t n,
-                                                   const uint32_t* __restrict__ sums) {
-  __shared__ uint32_t wsum[4];
-  const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-  uint32_t v[SCAN_ITEMS];
-  uint32_t s = 0;
-#pragma unroll
-  for (int i = 0; i < SCAN_ITEMS; ++i) {
-    v[i] = (base + i < n) ? in[base + i] : 0u;
-    s += v[i];
-  }
-  uint32_t total;
-  uint32_t run = sums[blockIdx.x] + block_exclusive_scan(s, wsum, total);
-#pragma unroll
-  for (int i = 0; i < SCAN_ITEMS; ++i) {
-    if (base + i < n) out[base + i] = run;
-    run += v[i];
-  }
-}
-
-static hipError_t exclusive_scan(uint32_t* data, int64_t n, uint32_t* sums, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const int64_t nb = cdiv(n, SCAN_TILE);
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(256), 0, st, data, n, sums);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, sums, nb);
-  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(256), 0, st, data, data, n, sums);
-  return hipGetLastError();
 }
 
 // Per digit d (one workgroup each) of a radix pass: exclusive scan, in place,
@@ -179,15 +135,9 @@ __device__ __forceinline__ uint32_t sort_key(const void* keys, int64_t i) {
 }
 
 template <int KM>
-__global__ __launch_bounds__(256) void k_radix_hist(const void* __restrict__ keys, int64_t Lmax,
-                                                    const uint32_t* __restrict__ Ldev, int shift,
-                                                    int bits, int64_t nblk,
+__global__ __launch_bounds__(256) void k_radix_hist(const void* __restrict__ keys, int64_t L,
+                                                    int shift, int bits, int64_t nblk,
                                                     uint32_t* __restrict__ hist) {
-  const int64_t L = (Ldev && (int64_t)*Ldev < Lmax) ? (int64_t)*Ldev : Lmax;
-  if ((int64_t)blockIdx.x * SORT_TILE >= L) {  // a tile past the count: empty
-    hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = 0u;
-    return;
-  }
   __shared__ uint32_t h[RADIX];
   h[threadIdx.x] = 0;
   __syncthreads();
@@ -213,18 +163,14 @@ __global__ __launch_bounds__(256) void k_radix_hist(const void* __restrict__ key
 template <int KM>
 __global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ keys_in,
                                                        const uint32_t* __restrict__ vals_in,
-                                                       int64_t Lmax,
-                                                       const uint32_t* __restrict__ Ldev, int shift,
-                                                       int bits, int64_t nblk,
+                                                       int64_t L, int shift, int bits, int64_t nblk,
                                                        const uint32_t* __restrict__ offsets,
                                                        const uint32_t* __restrict__ totals,
                                                        uint32_t* __restrict__ keys_out,
                                                        uint32_t* __restrict__ vals_out) {
   constexpr int PER_WAVE = SORT_TILE / 4;  // contiguous keys ranked by one wave
   constexpr int ROUNDS = PER_WAVE / WAVE;
-  const int64_t L = (Ldev && (int64_t)*Ldev < Lmax) ? (int64_t)*Ldev : Lmax;
   const int64_t tile = (int64_t)blockIdx.x * SORT_TILE;
-  if (tile >= L) return;  // whole block: nothing to move
   __shared__ uint32_t run[RADIX];      // global start of each digit's run for this tile
   __shared__ uint32_t tstart[RADIX];   // start of each digit within the tile
   __shared__ uint32_t wcnt[4][RADIX];  // per-wave digit counts, then per-wave starts
@@ -388,10 +334,9 @@ constexpr int CHAIN_TILE = 1024 * CHAIN_ITEMS;
 constexpr int ONE_ITEMS = 8;
 constexpr int64_t ONE_MAX = 1024 * ONE_ITEMS;        // keys one workgroup sorts by itself
 // Lookups the chain takes: 2^19 of them 25 us faster than three launches a
-// pass, 2^20 no faster (729 / 735 us with the rows), 2^21 5% slower.  Slot rows,
-// which are packed first otherwise, up to SORT_SLOTS_MAX (search backward, S =
-// 1024, 4 heads, k = 32: 4096 tokens 142 -> 108 us, 8192 201 -> 178, 16384
-// 341 -> 373).
+// pass, 2^20 no faster (729 / 735 us with the rows), 2^21 5% slower.  Slot rows
+// come here only where they are few (the search backward counts its sub-keys
+// otherwise).
 constexpr int64_t CHAIN_MAX = (int64_t)1 << 19;
 
 // Where a sort takes its items: item i of an int64 or u32 array (value: the
@@ -908,20 +853,17 @@ size_t long_partial_bytes(int64_t L, int D) {
 }
 
 // Stable LSD radix sort of the source's keys (< 2^key_bits) with their
-// positions (or vals_in) as values, then the segment starts of equal keys:
+// positions as values, then the segment starts of equal keys:
 // seg[0..U] in b.seg, U in b.misc[0]; the segments of more than thresh items in
 // long_list, their number in b.misc[1].  *ks / *vs receive the sorted arrays.
-// L is the item count, or its upper bound: of slots, or of items when Ldev
-// (device memory) holds their count.
+// L is the item count, of slots its upper bound.
 static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, const SortedWs& b,
                                 uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
-                                const uint32_t** vs, hipStream_t st,
-                                const uint32_t* vals_in = nullptr,
-                                const uint32_t* Ldev = nullptr) {
+                                const uint32_t** vs, hipStream_t st) {
   const bool slots = src.counts != nullptr;
-  const bool key64 = !slots && !vals_in;
+  const uint32_t* Ldev = nullptr;  // the items' number, when on the device
   uint32_t *kout = b.keys_a, *vout = b.vals_a;
-  if ((key64 || slots) && L <= ONE_MAX) {
+  if (L <= ONE_MAX) {
     *ks = kout;
     *vs = vout;
     if (slots)
@@ -933,7 +875,7 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
     return hipGetLastError();
   }
   const int passes = (key_bits + RADIX_BITS - 1) / RADIX_BITS;
-  if (slots || (key64 && L <= CHAIN_MAX)) {
+  if (slots || L <= CHAIN_MAX) {
     const int64_t nblk = cdiv(L, CHAIN_TILE);  // up to four histograms fit b.hist: 1024 * nblk <= L
     const dim3 g((unsigned)nblk), blk(1024);
     const int bits0 = key_bits < RADIX_BITS ? key_bits : RADIX_BITS;
@@ -970,19 +912,19 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
     if (e != hipSuccess) return e;
     const int64_t nblk = cdiv(L, SORT_TILE);
     const void* kin = src.keys;
-    const uint32_t* vin = vals_in;
+    const uint32_t* vin = nullptr;
     for (int shift = 0, pass = 0; shift < key_bits; shift += RADIX_BITS, ++pass) {
       const int bits = (key_bits - shift) < RADIX_BITS ? (key_bits - shift) : RADIX_BITS;
       const dim3 g((unsigned)nblk), blk(256);
-      if (pass > 0 || vals_in)
-        hipLaunchKernelGGL(k_radix_hist<SRC_NEXT>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
+      if (pass > 0)
+        hipLaunchKernelGGL(k_radix_hist<SRC_NEXT>, g, blk, 0, st, kin, L, shift, bits, nblk, b.hist);
       else
-        hipLaunchKernelGGL(k_radix_hist<SRC_I64>, g, blk, 0, st, kin, L, Ldev, shift, bits, nblk, b.hist);
+        hipLaunchKernelGGL(k_radix_hist<SRC_I64>, g, blk, 0, st, kin, L, shift, bits, nblk, b.hist);
       hipLaunchKernelGGL(k_scan_digits, dim3(RADIX), blk, 0, st, b.hist, nblk, b.totals);
-      if (pass > 0 || vals_in)
-        hipLaunchKernelGGL(k_radix_scatter<SRC_NEXT>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
+      if (pass > 0)
+        hipLaunchKernelGGL(k_radix_scatter<SRC_NEXT>, g, blk, 0, st, kin, vin, L, shift, bits, nblk, b.hist, b.totals, kout, vout);
       else
-        hipLaunchKernelGGL(k_radix_scatter<SRC_I64>, g, blk, 0, st, kin, vin, L, Ldev, shift, bits, nblk, b.hist, b.totals, kout, vout);
+        hipLaunchKernelGGL(k_radix_scatter<SRC_I64>, g, blk, 0, st, kin, vin, L, shift, bits, nblk, b.hist, b.totals, kout, vout);
       kin = kout;
       vin = vout;
       if (kout == b.keys_a) { kout = b.keys_b; vout = b.vals_b; }
@@ -1000,34 +942,17 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
   return hipGetLastError();
 }
 
-// Sort of u32 keys for other kernels of the library: either up to
-// SORT_SLOTS_MAX slots in rows of k with their counts (values: the slots), or
-// up to Lmax (key, value) pairs, their count in device memory (*Ldev), in the
-// arrays sort_u32_inputs returns for this workspace (the first radix pass reads
-// them, the second overwrites them).
-void sort_u32_inputs(void* ws, int64_t Lmax, uint32_t** keys_in, uint32_t** vals_in) {
-  SortedWs b = carve(ws, Lmax);
-  *keys_in = b.keys_b;
-  *vals_in = b.vals_b;
-}
-
-hipError_t sort_u32_segments(const SortSrc* slots, int64_t Lmax, const uint32_t* Ldev, int key_bits,
-                             void* ws, uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
-                             const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
-                             const uint32_t** nlong, hipStream_t st) {
-  SortedWs b = carve(ws, Lmax);
+// Sort of up to nslots slots in rows of k with their counts (values: the slots)
+// for other kernels of the library.
+hipError_t sort_slots_segments(const SortSrc& slots, int64_t nslots, int key_bits, void* ws,
+                               uint32_t thresh, uint32_t* long_list, const uint32_t** ks,
+                               const uint32_t** vs, const uint32_t** seg, const uint32_t** nseg,
+                               const uint32_t** nlong, hipStream_t st) {
+  SortedWs b = carve(ws, nslots);
   *seg = b.seg;
   *nseg = b.misc;
   *nlong = b.misc + 1;
-  if (slots) return sort_segments(*slots, Lmax, key_bits, b, thresh, long_list, ks, vs, st);
-  return sort_segments(SortSrc{b.keys_b, nullptr, 0}, Lmax, key_bits, b, thresh, long_list, ks, vs, st,
-                       b.vals_b, Ldev);
-}
-
-// Exclusive prefix sum of n u32 in place; sums needs scan_scratch_u32(n) entries.
-size_t scan_scratch_u32(int64_t n) { return (size_t)(cdiv(n, SCAN_TILE) + 1); }
-hipError_t scan_exclusive_u32(uint32_t* data, int64_t n, uint32_t* sums, hipStream_t st) {
-  return exclusive_scan(data, n, sums, st);
+  return sort_segments(slots, nslots, key_bits, b, thresh, long_list, ks, vs, st);
 }
 
 // Rows listed with the segments (more than LONG_SEG lookups) are cut into chunks
