@@ -14,7 +14,6 @@ there is no fallback: without the built library every call raises.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import functools
 import os
@@ -129,28 +128,25 @@ def _dt(t: torch.Tensor) -> int:
 
 def _dev(*ts: torch.Tensor) -> None:
     for t in ts:
-        if t is None:
-            continue
-        if not t.is_cuda:
-            raise ValueError("tensors must be on the GPU")
-        if not t.is_contiguous():
-            raise ValueError("tensors must be contiguous")
+        if t is not None:
+            if not t.is_cuda:
+                raise ValueError("tensors must be on the GPU")
+            if not t.is_contiguous():
+                raise ValueError("tensors must be contiguous")
 
 
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# A small call is bound by the host: of the 21 us of a decode step of three
+# kernels and the 65 us of a training step of 256 tokens, torch's stream object
+# alone took 4 us a call, so the handle is asked for directly, and the
+# stream context is entered only where a stream is given.
 def _stream(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
-
-
-def _on(stream):
-    """Context making `stream` (if given) torch's current stream, so that the
-    outputs and workspaces allocated inside belong to the stream the library
-    launches on and any zero-fill is ordered before the launch."""
-    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _launches_on_stream(fn):
@@ -160,7 +156,9 @@ def _launches_on_stream(fn):
     ordered before the launch on that stream."""
     @functools.wraps(fn)
     def wrapper(*args, stream=None, **kw):
-        with _on(stream):
+        if stream is None:
+            return fn(*args, **kw)
+        with torch.cuda.stream(stream):
             return fn(*args, stream=stream, **kw)
     return wrapper
 
