@@ -32,7 +32,6 @@
 namespace pk {
 
 constexpr int SPLIT_RECS = 64;  // record slots per token and part
-constexpr float LOWEST = -3.402823466e38f;
 
 template <typename T, int NSTEP, int W, int TPW>
 __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
@@ -175,10 +174,10 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
         __builtin_amdgcn_sched_barrier(0);
       }
       const int r0 = (wave * TPW + i) * 32;
-      if (part * R + r0 + 32 > S) {  // rows past S are never selected
+      if (part * R + r0 + 32 > S) {  // rows past S: NaN, at or above no threshold
 #pragma unroll
         for (int j = 0; j < 16; ++j)
-          acc[j] = part * R + r0 + acc_row(j, kh) < S ? acc[j] : -INFINITY;
+          acc[j] = part * R + r0 + acc_row(j, kh) < S ? acc[j] : __uint_as_float(0xFFC00000u);
       }
 #pragma unroll
       for (int j = 0; j < 16; j += 4)
@@ -220,7 +219,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
         float mx = v[a][0];
 #pragma unroll
         for (int e = 1; e < E; ++e) mx = fmaxf(mx, v[a][e]);
-        u[a] = f32_to_ordered(mx);
+        u[a] = mx == mx ? f32_to_ordered(mx) : 0u;  // 0: no row in this lane
         thr[a] = 0;
       }
 #pragma unroll
@@ -234,8 +233,9 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
       for (int a = 0; a < NT; ++a) {
         if (tl + a * W >= nt) break;  // the same for the whole wave
         uint2* const st = stage[wave][a];
-        // as a float; the lowest finite one where fewer than k lanes hold a row
-        const float tf = thr[a] < 0x00800000u ? LOWEST : ordered_to_f32(thr[a]);
+        // as a float; -inf (which a product past the float range may be) where
+        // fewer than k lanes hold a row
+        const float tf = thr[a] < 0x00800000u ? -INFINITY : ordered_to_f32(thr[a]);
         uint32_t cnt = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(v[a][e] >= tf));

@@ -112,3 +112,33 @@ def test_few_rows_variants_equal_many_rows(gpu_lib, T):
         scale = score.abs().max().item()
         assert (score - many[2].view(reps, *score.shape)).abs().max().item() <= n * 2 ** -23 * scale
         assert (w - many[1].view(reps, *w.shape)).abs().max().item() <= 1e-5
+
+
+@pytest.mark.parametrize("S,dt", [(300, F32), (512, BF), (2049, BF)])
+def test_few_rows_products_past_the_float_range(gpu_lib, S, dt):
+    """Finite inputs whose products overflow to -inf for all but m < k sub-keys:
+    the half lists go on with the -inf rows in index order, and no rank pair
+    reads an empty record."""
+    H, d, k, m, T = 2, 32, 8, 5, 3
+    q, K = int_tensor((T, H, 2 * d), 311, dt), int_tensor((H, 2, S, d), 312, dt)
+    q[:, :, 0] = q[:, :, d] = 1e30
+    K[..., 0] = -3e38
+    K[:, :, [S - 1, 7, S // 2, 64, 3], 0] = 0
+    assert torch.isfinite(q).all() and torch.isfinite(K).all()
+    idx, w, score, hidx = pk.mem_search(q.cuda(), K.cuda(), k, want_half=True)
+    torch.cuda.synchronize()
+    qd = q.double().reshape(T, H, 2, d)
+    z = torch.einsum("thpd,hpsd->thps", qd, K.double())
+    z[z < -3.4e38] = -float("inf")
+    order = torch.sort(z, dim=-1, descending=True, stable=True)
+    hv, hi = order.values[..., :k], order.indices[..., :k]
+    assert torch.isinf(hv[..., m:]).all() and torch.isfinite(hv[..., :m]).all()
+    np.testing.assert_array_equal(hidx.cpu().numpy(), hi.numpy())
+    zz = (hv[:, :, 0, :m, None] + hv[:, :, 1, None, :m]).reshape(T, H, -1)
+    ii = (hi[:, :, 0, :m, None] * S + hi[:, :, 1, None, :m]).reshape(T, H, -1)
+    ii, o = torch.sort(ii, dim=-1)  # equal sums: lower index first
+    zz = torch.gather(zz, -1, o)
+    zz, o = torch.sort(zz, dim=-1, descending=True, stable=True)
+    np.testing.assert_array_equal(idx.cpu().numpy(), torch.gather(ii, -1, o)[..., :k].numpy())
+    np.testing.assert_array_equal(h64(score), zz[..., :k].numpy())
+    assert normwise(h64(w), torch.softmax(zz[..., :k], -1).numpy()) <= TOL_F32
