@@ -125,9 +125,13 @@ size_t bwd_ws_bytes(int64_t T, int H, int k, int D, int mode) {
 // atomic adds when L*D <= 2^26 fp32 updates and D <= 1024, the sorted
 // strategy otherwise.  Measured on MI355X (uniform indices over 2^20 rows,
 // D = 64..2048, L = 32K..2M): the atomic kernel costs about 3.5 ps per
-// updated element plus one launch, the sort a fixed ~0.1 ms (eleven
-// launches) plus its row streaming, so atomics win only small batches; at
-// D = 2048 the sort wins from 256 tokens on.  PKMEM_BWD_MODE=atomic|sorted in
+// updated element plus one launch, the sort a fixed ~0.05 ms (its launches;
+// up to 2^19 lookups one per pass) plus its row streaming, so atomics win only
+// small batches: D = 64, 524288 lookups 0.11 against 0.16 ms, but D = 128,
+// 1048576 lookups 0.44 against 0.38.  At D = 2048 the sort wins from 256 tokens
+// on.  The line is part of the interface (pkmem.h); at its upper edge for D of
+// 512 and more the sort is by now up to 11% the faster one (D = 1024, 32768
+// lookups 0.137 against 0.122 ms).  PKMEM_BWD_MODE=atomic|sorted in
 // the environment overrides the choice (read at every call).
 int resolve_mode(int mode, int D, int64_t L) {
   if (mode != PKMEM_BWD_AUTO) return mode;
