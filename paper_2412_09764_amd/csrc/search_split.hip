@@ -248,13 +248,18 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
             base += (uint32_t)__popcll(m);
           }
         } else {  // the exact top k of the part
-          uint32_t x = 0;  // the k-th largest score (at least k lie at or above tf)
+          // The k-th largest score (at least k lie at or above tf).  A score that
+          // is no number (products past the float range of both signs) counts
+          // below every other, as in the compares that take the records.
+          uint32_t x = 0;
           for (int b = 31; b >= 0; --b) {
             const uint32_t c = x | (1u << b);
             uint32_t have = 0;
 #pragma unroll
-            for (int e = 0; e < E; ++e)
-              have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f32_to_ordered(v[a][e]) >= c));
+            for (int e = 0; e < E; ++e) {
+              const uint32_t o = v[a][e] == v[a][e] ? f32_to_ordered(v[a][e]) : 0u;
+              have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(o >= c));
+            }
             if (have >= (uint32_t)k) x = c;
           }
           const float xf = ordered_to_f32(x);
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
             if (v[a][e] == xf && at < (uint32_t)k) put(st, at, v[a][e], e);
             base += (uint32_t)__popcll(m);
           }
-          cnt = (uint32_t)k;
+          cnt = base < (uint32_t)k ? base : (uint32_t)k;  // the records staged
         }
         // Slots rotated by part, so that the merge's lanes (every 64th slot of
         // the token's each) hold about as many records each.

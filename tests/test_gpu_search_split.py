@@ -142,3 +142,47 @@ def test_few_rows_products_past_the_float_range(gpu_lib, S, dt):
     np.testing.assert_array_equal(idx.cpu().numpy(), torch.gather(ii, -1, o)[..., :k].numpy())
     np.testing.assert_array_equal(h64(score), zz[..., :k].numpy())
     assert normwise(h64(w), torch.softmax(zz[..., :k], -1).numpy()) <= TOL_F32
+
+
+def _with_nan_rows(S, H, d, T, nan, seed):
+    """Integer queries and sub-keys whose products overflow with both signs for
+    the sub-keys of `nan` (so that their scores are no number): all inputs
+    finite.  bf16 only: in fp32 the chain's steps are fused, and +inf plus an
+    unrounded product stays +inf.  Returns q, K and the exact scores with those
+    at -inf."""
+    q, K = int_tensor((T, H, 2 * d), seed, BF), int_tensor((H, 2, S, d), seed + 1, BF)
+    for p in (0, d):
+        q[:, :, p] = q[:, :, p + 16] = 1e30
+    K[..., 0] = K[..., 16] = 0
+    # in different steps of the product's chain: +inf first, then -inf added
+    K[:, :, nan, 0], K[:, :, nan, 16] = 3e38, -3e38
+    assert torch.isfinite(q).all() and torch.isfinite(K).all()
+    z = torch.matmul(q.double().reshape(T, H, 2, 1, d), K.double().transpose(-1, -2).contiguous()[None])
+    z = z.reshape(T, H, 2, S)
+    z[..., nan] = -float("inf")
+    return q, K, z
+
+
+@pytest.mark.parametrize("S,k,T", [(512, 64, 40), (700, 48, 33), (300, 64, 5), (2049, 64, 33),
+                                   (8192, 32, 33), (1000, 17, 33)])
+def test_few_rows_scores_that_are_no_number(gpu_lib, S, k, T):
+    """Sub-keys whose score is no number are never selected while k others are
+    there, also where a part has more records than slots (ties, k = 64)."""
+    print(f"[few-nan] {S} {k} {T}", flush=True)
+    H, d = 2, 32
+    nan = torch.rand(S, generator=torch.Generator().manual_seed(S)) < 0.3
+    nan[S - 1] = nan[0] = True
+    q, K, z = _with_nan_rows(S, H, d, T, nan, 411)
+    idx, w, score, hidx = pk.mem_search(q.cuda(), K.cuda(), k, want_half=True)
+    torch.cuda.synchronize()
+    order = torch.sort(z, dim=-1, descending=True, stable=True)
+    hv, hi = order.values[..., :k], order.indices[..., :k]
+    assert torch.isfinite(hv).all()
+    np.testing.assert_array_equal(hidx.cpu().numpy(), hi.numpy())
+    zz = (hv[:, :, 0, :, None] + hv[:, :, 1, None, :]).reshape(T, H, -1)
+    ii = (hi[:, :, 0, :, None] * S + hi[:, :, 1, None, :]).reshape(T, H, -1)
+    ii, o = torch.sort(ii, dim=-1)  # equal sums: lower index first
+    zz, o = torch.sort(torch.gather(zz, -1, o), dim=-1, descending=True, stable=True)
+    np.testing.assert_array_equal(idx.cpu().numpy(), torch.gather(ii, -1, o)[..., :k].numpy())
+    np.testing.assert_array_equal(h64(score), zz[..., :k].numpy())
+    assert normwise(h64(w), torch.softmax(zz[..., :k], -1).numpy()) <= TOL_F32
