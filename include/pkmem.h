@@ -26,7 +26,8 @@
  *     the host before any launch) or a HIP error (PKMEM_ERR_HIP).  No call aborts
  *     or throws; mem_last_error() gives a message for the calling thread.
  *   - Inputs must be finite.  Indices passed to the bag calls must lie in [0, N)
- *     and are not range-checked (they normally come from mem_search).
+ *     and are not range-checked (they normally come from mem_search, whose
+ *     product-key indices lie in [0, S*S) whatever the scores).
  *
  * Readings where the paper is silent:
  *   - H heads: per token, H independent queries and sub-key pairs; each head

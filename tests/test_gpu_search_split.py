@@ -186,3 +186,31 @@ def test_few_rows_scores_that_are_no_number(gpu_lib, S, k, T):
     np.testing.assert_array_equal(idx.cpu().numpy(), torch.gather(ii, -1, o)[..., :k].numpy())
     np.testing.assert_array_equal(h64(score), zz[..., :k].numpy())
     assert normwise(h64(w), torch.softmax(zz[..., :k], -1).numpy()) <= TOL_F32
+
+
+@pytest.mark.parametrize("m", [0, 1, 5])
+@pytest.mark.parametrize("S", [512, 2049])
+def test_too_few_scores_that_are_numbers(gpu_lib, S, m):
+    """A half with m < k such scores: the half lists go on with row 0 and every
+    index lies in the table (it may be handed to the bag), on the path for few
+    rows and on the one for many; with enough pairs left the selection is exact."""
+    print(f"[too-few] {S} {m}", flush=True)
+    H, d, k, T = 2, 32, 8, 4
+    nan = torch.ones(S, dtype=torch.bool)
+    nan[[S - 1, 7, S // 2, 64, 3][:m]] = False
+    q, K, z = _with_nan_rows(S, H, d, T, nan, 421)
+    order = torch.sort(z, dim=-1, descending=True, stable=True)
+    hv, hi = order.values[..., :m], order.indices[..., :m]
+    zz = (hv[:, :, 0, :, None] + hv[:, :, 1, None, :]).reshape(T, H, -1)
+    ii = (hi[:, :, 0, :, None] * S + hi[:, :, 1, None, :]).reshape(T, H, -1)
+    ii, o = torch.sort(ii, dim=-1)
+    zz, o = torch.sort(torch.gather(zz, -1, o), dim=-1, descending=True, stable=True)
+    want = torch.gather(ii, -1, o)[..., :k]
+    for reps in (1, -(-(1 << 26) // (2 * T * H * S))):  # rows * S >= 2^26
+        idx, w, score, hidx = pk.mem_search(q.cuda().repeat(reps, 1, 1), K.cuda(), k, want_half=True)
+        torch.cuda.synchronize()
+        idx, hidx = idx.cpu().view(reps, T, H, k), hidx.cpu().view(reps, T, H, 2, k)
+        assert int(idx.min()) >= 0 and int(idx.max()) < S * S
+        assert (hidx[..., :m] == hi).all() and (hidx[..., m:] == 0).all()
+        c = want.shape[-1]  # pairs of two numbers among the k
+        assert (idx[..., :c] == want).all()
