@@ -694,7 +694,9 @@ __global__ __launch_bounds__(64 * W, 4) void k_score_topk(
     lo_c = hi_c;
   }
   sweep(0, P1, collect_tile);
-  if (lane == 0) cnts[wr] = wcnt;
+  // The last tile's waves past the tokens have no run: search_ws holds a count
+  // per 32 tokens only, and the thresholds follow it.
+  if (lane == 0 && tile * (32 * W) + wave * 32 < ntok) cnts[wr] = wcnt;
 }
 
 // Pass 3 as a kernel of its own: one workgroup per wave run (32 tokens of one
