@@ -273,27 +273,29 @@ __global__ __launch_bounds__(256) void k_search_bwd_q32(
   const int e0 = j * N;
   const bool has = e0 < d;
   const int eo = has ? e0 : 0;
-  // The leaders first, as byte offsets into the head's two tables (at most
-  // 2 * 8192 rows of 512 bytes), then row 0 of the half with weight 0: a row
-  // costs an LDS read at a constant offset and one addition.
+  // The leaders' list, as byte offsets into the head's two tables (at most
+  // 2 * 8192 rows of 512 bytes): a row costs an LDS read at a constant offset
+  // and one addition.  The last batch of QU is filled with its own first leader
+  // at weight 0, so that only sub-keys the row selected are ever read (an
+  // infinity in another one stays out of the sum); each half stops at its own.
   const uint32_t row_bytes = (uint32_t)d * (uint32_t)sizeof(T);
-  const uint32_t half0 = p == 0 ? 0u : (uint32_t)S * row_bytes;
-  list[wave][p][leader ? pos : cnt + (uint32_t)j - pos] =
-      make_uint2(leader ? half0 + (uint32_t)mine * row_bytes : half0,
-                 leader ? __float_as_uint(gsum) : 0u);
+  uint2* const lst = list[wave][p];
+  if (leader)
+    lst[pos] = make_uint2((p == 0 ? 0u : (uint32_t)S * row_bytes) + (uint32_t)mine * row_bytes,
+                          __float_as_uint(gsum));
+  static_assert((QU & (QU - 1)) == 0 && 32 % QU == 0, "batches of the 32 list entries");
+  const uint32_t last = cnt & ~(uint32_t)(QU - 1);  // start of a last, partial batch
+  if ((uint32_t)j >= cnt && (uint32_t)j < last + QU && last < cnt) lst[j] = make_uint2(lst[last].x, 0u);
   const char* const kb = reinterpret_cast<const char*>(subkeys + (size_t)(h * 2) * S * d);
   const uint32_t lo = (uint32_t)eo * (uint32_t)sizeof(T);
-  const uint32_t n0 = (uint32_t)__popcll(lm & 0xFFFFFFFFull), n1 = (uint32_t)__popcll(lm >> 32);
-  const uint32_t rows = n0 > n1 ? n0 : n1;  // uniform
   float acc[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) acc[i] = 0.f;
-  static_assert(32 % QU == 0, "batches of the 32 list entries");
-  for (uint32_t b = 0; b < rows; b += QU) {
+  for (uint32_t b = 0; b < cnt; b += QU) {
     Seg ks[QU];
     uint2 e[QU];
 #pragma unroll
-    for (int u = 0; u < QU; ++u) e[u] = list[wave][p][b + u];
+    for (int u = 0; u < QU; ++u) e[u] = lst[b + u];
 #pragma unroll
     for (int u = 0; u < QU; ++u) ks[u].load(reinterpret_cast<const T*>(kb + (e[u].x + lo)));
 #pragma unroll

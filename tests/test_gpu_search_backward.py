@@ -152,3 +152,31 @@ def test_search_backward_long_segments(gpu_lib, qnorm):
     # the hot sub-key rows themselves (the long segments)
     for p, rows in ((0, [0, 1]), (1, [0, 1, 2, 3])):
         assert normwise(h64(a[1])[:, p, rows], ref["grad_K"][:, p, rows]) <= TOL_F32
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("k", [1, 5, 8, 17, 32, 40])
+def test_rows_not_selected_leave_grad_q_alone(gpu_lib, k, dt):
+    """Sub-keys that no lookup names are not read into grad_q: with every one of
+    them infinite (the first and the last of each half among them) it is the
+    finite sum over those named, whole numbers and so exact."""
+    T, H, S, d = 37, 2, 50, 32
+    dtype = {"bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    print(f"[sbwd-unselected] {k} {dt}", flush=True)
+    g = torch.Generator().manual_seed(700 + k)
+    # half 0 takes few sub-keys, half 1 many: the halves' counts differ
+    i1 = torch.randint(1, 4, (T, H, k), generator=g)
+    i2 = torch.randint(1, S - 1, (T, H, k), generator=g)
+    q = torch.randint(-2, 3, (T, H, 2 * d), generator=g).to(dtype)
+    K = torch.randint(-2, 3, (H, 2, S, d), generator=g).to(dtype)
+    K[:, 0, 0] = K[:, 0, 4:] = K[:, 1, 0] = K[:, 1, S - 1] = float("inf")
+    gz = torch.randint(-2, 3, (T, H, k), generator=g).float()
+    gq, _ = gpu_lib.mem_search_backward(q.cuda(), K.cuda(), (i1 * S + i2).cuda(), gz.cuda())
+    torch.cuda.synchronize()
+    want = torch.zeros((T, H, 2 * d), dtype=torch.float64)
+    for h in range(H):
+        for p, i in enumerate((i1, i2)):
+            rows = K[h, p][i[:, h]].double()
+            want[:, h, p * d:(p + 1) * d] = (gz[:, h, :, None].double() * rows).sum(1)
+    assert torch.isfinite(want).all()
+    assert torch.equal(gq.cpu().double(), want)
