@@ -277,6 +277,7 @@ __global__ __launch_bounds__(64 * W) void k_bag_fwd_split(
         lk.get(G == 1 ? (j < nb ? j : b) : (j < nb ? j : 0), r, ww[u]);
         const bool live = j < nb && ok;
         v[u] = live ? ld16_nt(col + r * D) : uint4{0, 0, 0, 0};
+        ww[u] = live ? ww[u] : 0.f;  // an infinite weight times nothing is nothing
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {

@@ -56,3 +56,21 @@ def test_bag_of_few_tokens(gpu_lib, T, bag, D, dt, gated):
         if dtype is torch.bfloat16:
             t = t + 2 ** -8 * b.abs().max().item()
         assert (a.double() - b).abs().max().item() <= t
+
+
+@pytest.mark.parametrize("T,bag,D,dt", [(1, 9, 512, "bf16"), (3, 67, 520, "bf16"), (7, 33, 264, "f32"),
+                                        (9, 70, 64, "bf16"), (9, 300, 16, "bf16"), (4, 64, 8, "f32"),
+                                        (1, 128, 1024, "bf16")])
+def test_infinite_weight_stays_infinite(gpu_lib, T, bag, D, dt):
+    """An infinite weight on a positive row gives +inf, wherever in the bag it
+    stands: no lookup past a wave's own takes part."""
+    print(f"[bag-split-inf] {T} {bag} {D} {dt}", flush=True)
+    dtype = {"bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    V = torch.ones((5, D), dtype=dtype, device="cuda")
+    idx = torch.arange(bag).remainder(5).repeat(T, 1).cuda()
+    for j in sorted({0, 1, 8, bag // 2, bag - 1}):
+        w = torch.ones((T, bag), device="cuda")
+        w[:, j] = float("inf")
+        y = pk.mem_bag_forward(V, idx, w)
+        torch.cuda.synchronize()
+        assert (y == float("inf")).all(), j
