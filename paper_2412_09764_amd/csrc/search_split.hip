@@ -248,18 +248,19 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
             base += (uint32_t)__popcll(m);
           }
         } else {  // the exact top k of the part
-          // The k-th largest score (at least k lie at or above tf).  A score that
-          // is no number (products past the float range of both signs) counts
-          // below every other, as in the compares that take the records.
-          uint32_t x = 0;
+          // A score that is no number (products past the float range of both
+          // signs) counts below every other, as in the compares that take the
+          // records: its sign is set, as that of the rows past S is.
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            v[a][e] = v[a][e] == v[a][e] ? v[a][e] : __uint_as_float(0xFFC00000u);
+          uint32_t x = 0;  // the k-th largest score (at least k lie at or above tf)
           for (int b = 31; b >= 0; --b) {
             const uint32_t c = x | (1u << b);
             uint32_t have = 0;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-              const uint32_t o = v[a][e] == v[a][e] ? f32_to_ordered(v[a][e]) : 0u;
-              have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(o >= c));
-            }
+            for (int e = 0; e < E; ++e)
+              have += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f32_to_ordered(v[a][e]) >= c));
             if (have >= (uint32_t)k) x = c;
           }
           const float xf = ordered_to_f32(x);
