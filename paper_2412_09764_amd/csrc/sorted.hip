@@ -123,30 +123,45 @@ __global__ __launch_bounds__(256) void k_scan_digits(uint32_t* __restrict__ hist
 
 // ----------------------------------------------------------- radix sort ----
 // KM selects where a pass takes its items: SRC_I64 (an int64 array) and SRC_U32
-// (rows of u32 slots, see SortSrc) are first
-// passes (keys from an int64 or u32 array, values = item positions), SRC_NEXT
-// a later pass (keys and values from the previous pass's output).
+// (rows of u32 slots, see SortSrc) are first passes, SRC_NEXT a later pass (keys
+// and values from the previous pass's output).
 constexpr int SRC_I64 = 0, SRC_U32 = 1, SRC_NEXT = 2;
 
+// Key of a pass's item i; false where there is none.  First passes: item i of
+// the int64 array (value: the position), or slot i of rows of k u32 keys of
+// which row r fills its first counts[r] (the others are dropped; value: the
+// slot).
 template <int KM>
-__device__ __forceinline__ uint32_t sort_key(const void* keys, int64_t i) {
-  if constexpr (KM == SRC_I64) return (uint32_t)reinterpret_cast<const int64_t*>(keys)[i];
-  else return reinterpret_cast<const uint32_t*>(keys)[i];
+__device__ __forceinline__ bool item_key(const SortSrc& src, int64_t i, int64_t L, uint32_t& key) {
+  if (i >= L) return false;
+  if constexpr (KM == SRC_I64) {
+    key = (uint32_t)reinterpret_cast<const int64_t*>(src.keys)[i];
+  } else if constexpr (KM == SRC_NEXT) {
+    key = reinterpret_cast<const uint32_t*>(src.keys)[i];
+  } else {
+    const uint32_t r = (uint32_t)i / (uint32_t)src.k;
+    if ((uint32_t)i - r * (uint32_t)src.k >= src.counts[r]) return false;
+    key = reinterpret_cast<const uint32_t*>(src.keys)[i];
+  }
+  return true;
 }
 
+// Ldev: the item count of a later pass after one over slots (null: L).
 template <int KM>
-__global__ __launch_bounds__(256) void k_radix_hist(const void* __restrict__ keys, int64_t L,
-                                                    int shift, int bits, int64_t nblk,
+__global__ __launch_bounds__(256) void k_radix_hist(SortSrc src, int64_t L,
+                                                    const uint32_t* __restrict__ Ldev, int shift,
+                                                    int bits, int64_t nblk,
                                                     uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[RADIX];
   h[threadIdx.x] = 0;
   __syncthreads();
+  if (Ldev) L = *Ldev;
   const uint32_t mask = (1u << bits) - 1u;
   const int64_t tile = (int64_t)blockIdx.x * SORT_TILE;
 #pragma unroll 4
   for (int i = 0; i < SORT_ITEMS; ++i) {
-    const int64_t pos = tile + i * 256 + threadIdx.x;
-    if (pos < L) atomicAdd(&h[(sort_key<KM>(keys, pos) >> shift) & mask], 1u);
+    uint32_t key;
+    if (item_key<KM>(src, tile + i * 256 + threadIdx.x, L, key)) atomicAdd(&h[(key >> shift) & mask], 1u);
   }
   __syncthreads();
   hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
@@ -161,16 +176,16 @@ __global__ __launch_bounds__(256) void k_radix_hist(const void* __restrict__ key
 // sorted order and from there to its digits' runs, consecutive threads
 // writing consecutive addresses.  Keys of equal digit keep their order.
 template <int KM>
-__global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ keys_in,
-                                                       const uint32_t* __restrict__ vals_in,
-                                                       int64_t L, int shift, int bits, int64_t nblk,
-                                                       const uint32_t* __restrict__ offsets,
-                                                       const uint32_t* __restrict__ totals,
-                                                       uint32_t* __restrict__ keys_out,
-                                                       uint32_t* __restrict__ vals_out) {
+__global__ __launch_bounds__(256) void k_radix_scatter(
+    SortSrc src, const uint32_t* __restrict__ vals_in, int64_t L, const uint32_t* __restrict__ Ldev,
+    int shift, int bits, int64_t nblk, const uint32_t* __restrict__ offsets,
+    const uint32_t* __restrict__ totals, uint32_t* __restrict__ keys_out,
+    uint32_t* __restrict__ vals_out, uint32_t* __restrict__ total_out) {
   constexpr int PER_WAVE = SORT_TILE / 4;  // contiguous keys ranked by one wave
   constexpr int ROUNDS = PER_WAVE / WAVE;
   const int64_t tile = (int64_t)blockIdx.x * SORT_TILE;
+  if (Ldev) L = *Ldev;
+  if (tile >= L) return;  // the whole workgroup
   __shared__ uint32_t run[RADIX];      // global start of each digit's run for this tile
   __shared__ uint32_t tstart[RADIX];   // start of each digit within the tile
   __shared__ uint32_t wcnt[4][RADIX];  // per-wave digit counts, then per-wave starts
@@ -182,6 +197,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ 
     uint32_t all;
     const uint32_t dbase = block_exclusive_scan(totals[tid], wsum, all);
     run[tid] = dbase + offsets[(int64_t)tid * nblk + blockIdx.x];
+    if (total_out && blockIdx.x == 0 && tid == 0) *total_out = all;
   }
 #pragma unroll
   for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0;
@@ -190,12 +206,14 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ 
   const uint64_t below = (1ull << lane) - 1ull;
   const int64_t wbase = tile + (int64_t)wave * PER_WAVE;
   uint32_t key[ROUNDS], val[ROUNDS], rk[ROUNDS];
+  uint32_t have = 0;  // bit i: the lane has an item in round i
 #pragma unroll
   for (int i = 0; i < ROUNDS; ++i) {
     const int64_t pos = wbase + i * WAVE + lane;
-    const bool valid = pos < L;
-    key[i] = valid ? sort_key<KM>(keys_in, pos) : 0u;
+    key[i] = 0;
+    const bool valid = item_key<KM>(src, pos, L, key[i]);
     val[i] = valid ? (KM != SRC_NEXT ? (uint32_t)pos : vals_in[pos]) : 0u;
+    have |= valid ? 1u << i : 0u;
     const uint32_t dig = (key[i] >> shift) & mask;
     uint64_t peers = __ballot(valid);
     for (int b = 0; b < bits; ++b) {
@@ -208,10 +226,10 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ 
     if (valid && r == 0) wcnt[wave][dig] += (uint32_t)__popcll(peers);
   }
   __syncthreads();
+  uint32_t n;  // items of the tile
   {  // thread tid = digit: the tile's digit starts and each wave's start within it
     const uint32_t c0 = wcnt[0][tid], c1 = wcnt[1][tid], c2 = wcnt[2][tid], c3 = wcnt[3][tid];
-    uint32_t total;
-    const uint32_t st = block_exclusive_scan(c0 + c1 + c2 + c3, wsum, total);
+    const uint32_t st = block_exclusive_scan(c0 + c1 + c2 + c3, wsum, n);
     tstart[tid] = st;
     wcnt[0][tid] = st;
     wcnt[1][tid] = st + c0;
@@ -221,20 +239,17 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const void* __restrict__ 
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < ROUNDS; ++i) {
-    const int64_t pos = wbase + i * WAVE + lane;
-    if (pos < L) {
+    if ((have >> i) & 1u) {
       const uint32_t p = wcnt[wave][(key[i] >> shift) & mask] + rk[i];
       skey[p] = key[i];
       sval[p] = val[i];
     }
   }
   __syncthreads();
-  const int64_t left = L - tile;
-  const int n = left < SORT_TILE ? (int)left : SORT_TILE;
-  for (int e = tid; e < n; e += 256) {
+  for (uint32_t e = tid; e < n; e += 256) {
     const uint32_t kk = skey[e];
     const uint32_t dig = (kk >> shift) & mask;
-    const uint32_t dst = run[dig] + (uint32_t)e - tstart[dig];
+    const uint32_t dst = run[dig] + e - tstart[dig];
     keys_out[dst] = kk;
     vals_out[dst] = sval[e];
   }
@@ -326,36 +341,20 @@ __global__ __launch_bounds__(256) void k_seg_place(const uint32_t* __restrict__ 
 // the latency of 16 serial rounds per wave on a few workgroups (65536 keys:
 // 6 + 4 + 15 us a pass).  The chain takes one launch per pass after a first
 // histogram: workgroups of 16 waves with 4 rounds each; every scatter adds up
-// the tile counts before its own itself (at most 512 tiles) and counts the next
+// the tile counts before its own itself (at most 256 tiles) and counts the next
 // pass's digits of the tiles it writes to with integer atomics (the counts
 // cleared by the first launch).  The result is the same stable sort.
 constexpr int CHAIN_ITEMS = 4;                       // keys per thread
 constexpr int CHAIN_TILE = 1024 * CHAIN_ITEMS;
 constexpr int ONE_ITEMS = 8;
 constexpr int64_t ONE_MAX = 1024 * ONE_ITEMS;        // keys one workgroup sorts by itself
-// Lookups the chain takes: 2^19 of them 25 us faster than three launches a
-// pass, 2^20 no faster (729 / 735 us with the rows), 2^21 5% slower.  Slot rows
-// come here only where they are few (the search backward counts its sub-keys
-// otherwise).
-constexpr int64_t CHAIN_MAX = (int64_t)1 << 19;
-
-// Where a sort takes its items: item i of an int64 or u32 array (value: the
-// position), or slot i of rows of k u32 keys of which row r fills its first
-// counts[r] (the others are dropped; value: the slot).
-template <int KM>
-__device__ __forceinline__ bool first_key(const SortSrc& src, int64_t i, int64_t L, uint32_t& key) {
-  if constexpr (KM == SRC_I64) {
-    if (i >= L) return false;
-    key = (uint32_t)reinterpret_cast<const int64_t*>(src.keys)[i];
-    return true;
-  } else {
-    if (i >= L) return false;
-    const uint32_t r = (uint32_t)i / (uint32_t)src.k;
-    if ((uint32_t)i - r * (uint32_t)src.k >= src.counts[r]) return false;
-    key = reinterpret_cast<const uint32_t*>(src.keys)[i];
-    return true;
-  }
-}
+// Keys the chain takes.  Each workgroup reads every tile's counts, so past some
+// number three launches a pass are the faster form.  Lookups: 2^19 of them 25 us
+// faster in the chain, 2^20 no faster (729 / 735 us with the rows), 2^21 5%
+// slower.  Slots (the whole search backward, d = 32): 2^20 of them 172 in the
+// chain and 181 us in three launches a pass, 2^21 271 and 230, 3.3M (100 tokens
+// of 512 heads) 1719 and 1521.
+constexpr int64_t CHAIN_MAX = (int64_t)1 << 19, CHAIN_MAX_SLOTS = (int64_t)1 << 20;
 
 // Exclusive scan over the first 256 threads of a workgroup (thread = digit) of
 // their v; every thread of the workgroup takes part.
@@ -389,7 +388,7 @@ __global__ __launch_bounds__(1024) void k_chain_hist(SortSrc src, int64_t L, int
 #pragma unroll
   for (int i = 0; i < CHAIN_ITEMS; ++i) {
     uint32_t key;
-    if (first_key<KM>(src, (int64_t)blockIdx.x * CHAIN_TILE + i * 1024 + tid, L, key))
+    if (item_key<KM>(src, (int64_t)blockIdx.x * CHAIN_TILE + i * 1024 + tid, L, key))
       atomicAdd(&h[key & mask], 1u);
   }
   __syncthreads();
@@ -432,7 +431,7 @@ __global__ __launch_bounds__(1024) void k_chain_scatter(
       if (valid[i]) key[i] = reinterpret_cast<const uint32_t*>(src.keys)[pos];
       val[i] = valid[i] ? vals_in[pos] : 0u;
     } else {
-      valid[i] = first_key<KM>(src, pos, L, key[i]);
+      valid[i] = item_key<KM>(src, pos, L, key[i]);
       val[i] = (uint32_t)pos;
     }
   }
@@ -564,7 +563,7 @@ __global__ __launch_bounds__(1024) void k_sort_one(SortSrc src, int L, int key_b
       valid[i] = false;
       if (i < rounds) {
         if (shift == 0) {
-          valid[i] = first_key<KM>(src, pos, L, key[i]);
+          valid[i] = item_key<KM>(src, pos, L, key[i]);
           val[i] = (uint32_t)pos;
         } else if (pos < L) {
           valid[i] = true;
@@ -875,7 +874,7 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
     return hipGetLastError();
   }
   const int passes = (key_bits + RADIX_BITS - 1) / RADIX_BITS;
-  if (slots || L <= CHAIN_MAX) {
+  if (L <= (slots ? CHAIN_MAX_SLOTS : CHAIN_MAX)) {
     const int64_t nblk = cdiv(L, CHAIN_TILE);  // up to four histograms fit b.hist: 1024 * nblk <= L
     const dim3 g((unsigned)nblk), blk(1024);
     const int bits0 = key_bits < RADIX_BITS ? key_bits : RADIX_BITS;
@@ -911,26 +910,28 @@ static hipError_t sort_segments(const SortSrc& src, int64_t L, int key_bits, con
     hipError_t e = launch_fill_u32(b.misc, 0u, 2, st);
     if (e != hipSuccess) return e;
     const int64_t nblk = cdiv(L, SORT_TILE);
-    const void* kin = src.keys;
+    SortSrc in = src;
     const uint32_t* vin = nullptr;
-    for (int shift = 0, pass = 0; shift < key_bits; shift += RADIX_BITS, ++pass) {
+    for (int shift = 0; shift < key_bits; shift += RADIX_BITS) {
       const int bits = (key_bits - shift) < RADIX_BITS ? (key_bits - shift) : RADIX_BITS;
       const dim3 g((unsigned)nblk), blk(256);
-      if (pass > 0)
-        hipLaunchKernelGGL(k_radix_hist<SRC_NEXT>, g, blk, 0, st, kin, L, shift, bits, nblk, b.hist);
-      else
-        hipLaunchKernelGGL(k_radix_hist<SRC_I64>, g, blk, 0, st, kin, L, shift, bits, nblk, b.hist);
-      hipLaunchKernelGGL(k_scan_digits, dim3(RADIX), blk, 0, st, b.hist, nblk, b.totals);
-      if (pass > 0)
-        hipLaunchKernelGGL(k_radix_scatter<SRC_NEXT>, g, blk, 0, st, kin, vin, L, shift, bits, nblk, b.hist, b.totals, kout, vout);
-      else
-        hipLaunchKernelGGL(k_radix_scatter<SRC_I64>, g, blk, 0, st, kin, vin, L, shift, bits, nblk, b.hist, b.totals, kout, vout);
-      kin = kout;
+      uint32_t* total = slots && shift == 0 ? b.misc + 3 : nullptr;
+      auto pass = [&](auto hist, auto scatter) {
+        hipLaunchKernelGGL(hist, g, blk, 0, st, in, L, Ldev, shift, bits, nblk, b.hist);
+        hipLaunchKernelGGL(k_scan_digits, dim3(RADIX), blk, 0, st, b.hist, nblk, b.totals);
+        hipLaunchKernelGGL(scatter, g, blk, 0, st, in, vin, L, Ldev, shift, bits, nblk, b.hist,
+                           b.totals, kout, vout, total);
+      };
+      if (shift > 0) pass(k_radix_hist<SRC_NEXT>, k_radix_scatter<SRC_NEXT>);
+      else if (slots) pass(k_radix_hist<SRC_U32>, k_radix_scatter<SRC_U32>);
+      else pass(k_radix_hist<SRC_I64>, k_radix_scatter<SRC_I64>);
+      if (total) Ldev = total;
+      in = SortSrc{kout, nullptr, 0};
       vin = vout;
       if (kout == b.keys_a) { kout = b.keys_b; vout = b.vals_b; }
       else { kout = b.keys_a; vout = b.vals_a; }
     }
-    *ks = reinterpret_cast<const uint32_t*>(kin);
+    *ks = reinterpret_cast<const uint32_t*>(in.keys);
     *vs = vin;
   }
   const int64_t nb = cdiv(L, SCAN_TILE);

@@ -69,3 +69,28 @@ def test_search_backward_sort_sizes(gpu_lib, T, H, S, k, hot):
             rK[h, p].index_add_(0, i[:, h].reshape(-1), src.reshape(-1, d))
     assert torch.equal(gq.double(), rq)
     assert torch.equal(gK.double(), rK)
+
+
+@pytest.mark.parametrize("T,H,S,k", [(29, 512, 8192, 32), (40, 512, 8192, 32), (43, 300, 8190, 41)])
+def test_search_backward_of_many_heads(gpu_lib, T, H, S, k):
+    """Slots of many heads and few tokens, too few to count per sub-key: the
+    chain of passes up to 2^20 of them, three launches a pass beyond; rows of
+    which only some slots are filled, and some of none."""
+    print(f"[sbwd-heads] {T} {H} {S} {k} {2 * T * H * k}", flush=True)
+    d = 8
+    g = torch.Generator(device="cuda").manual_seed(77 + T)
+    idx = torch.randint(0, S * S, (T, H, k), generator=g, device="cuda")
+    idx[torch.rand((T, H, k), generator=g, device="cuda") < 0.3] = 5 * S + 3  # shared sub-keys
+    idx[torch.rand((T, H, 1), generator=g, device="cuda").expand(T, H, k) < 0.1] = -1
+    q = torch.randint(-2, 3, (T, H, 2 * d), generator=g, device="cuda").to(torch.bfloat16)
+    K = torch.zeros((H, 2, S, d), dtype=torch.bfloat16, device="cuda")
+    gz = torch.randint(-2, 3, (T, H, k), generator=g, device="cuda").float()
+    _, gK = pk.mem_search_backward(q, K, idx, gz, want_grad_q=False)
+    torch.cuda.synchronize()
+    want = torch.zeros((H * 2 * S, d), dtype=torch.float32, device="cuda")  # whole numbers: exact
+    live, safe = gz * (idx >= 0), idx.clamp(min=0)
+    heads = torch.arange(H, device="cuda")[None, :, None]
+    for p, i in enumerate((safe // S, safe % S)):
+        src = live[..., None] * q[:, :, None, p * d:(p + 1) * d].float()
+        want.index_add_(0, ((heads * 2 + p) * S + i).reshape(-1), src.reshape(-1, d))
+    assert torch.equal(gK.reshape(-1, d), want)
