@@ -767,17 +767,24 @@ size_t search_backward_ws_bytes(int64_t T, int H, int k) {
 // to 8192 slots one workgroup sorts them all in one launch instead of three.
 // The counts, totals and starts have to fit the radix sort's share of the
 // workspace (sorted_workspace_bytes holds at least 6 words per slot, the pairs
-// take 2), which larger tiles give for T * k >= S; below that the chained
-// radix sort is taken.
+// take 2), which larger tiles give for T * k >= S; below that the radix sort is
+// taken.  It is also taken where S / 2 slots are many tokens, whose chain then
+// lasts longer than its passes (radix / counting sort, H = 1, k = 1, S = 8192, 8192
+// tokens 48 / 1528; k = 4, S = 2048, 4096 tokens, tiles of 256, 45 / 77; H = 4,
+// k = 8, S = 8192, 32768 tokens, tiles of 512, 230 / 290; but 54 / 48 at k = 16,
+// S = 2048, 4096 tokens, tiles of 64).  Tiles of 128 break even at about 2^20
+// slots: k = 32, S = 8192, H = 1, 8192 tokens 87 / 107, H = 2 145 / 136.
+constexpr int64_t BIN_TILE = 64, BIN_TILE_MANY = 128, BIN_MANY = (int64_t)1 << 20;
 static int bin_tile_tokens(int64_t T, int H, int S, int k) {
   const int64_t np = 2 * T * H * k;
   if (np <= 8192) return 0;
   int tile = 16;
   while (tile * k < S / 2) tile *= 2;
+  auto fits = [&](int t) { return ((T + t - 1) / t + 2) * 2 * H * S + 192 <= 4 * np; };
+  while (tile < T && !fits(tile)) tile *= 2;
+  if (tile > (np >= BIN_MANY ? BIN_TILE_MANY : BIN_TILE) || !fits(tile)) return 0;
   while (2 * H * (T / tile) > 2048) tile *= 2;
-  while (tile < T && ((T + tile - 1) / tile + 2) * 2 * H * S + 192 > 4 * np) tile *= 2;
-  const int64_t ntile = (T + tile - 1) / tile;
-  return (ntile + 2) * 2 * H * S + 192 <= 4 * np ? tile : 0;
+  return tile;
 }
 
 template <typename T>

@@ -42,3 +42,13 @@ def test_subkey_gradients_exact(gpu_lib, T, H, S, k, hot):
             src = live[:, h, :, None] * q[:, h, None, p * d:(p + 1) * d].double()
             want[h, p].index_add_(0, i[:, h].reshape(-1), src.reshape(-1, d))
     assert torch.equal(gK.double(), want)
+
+
+@pytest.mark.parametrize("T,H,S,k", [
+    (520, 1, 1024, 8), (520, 1, 1026, 8),            # tiles of 64 tokens; 128 of them: radix
+    (32768, 2, 2048, 8), (32767, 2, 2048, 8),        # tiles of 128 from 2^20 slots up
+    (33000, 2, 4100, 8), (4097, 1, 8192, 2),         # tiles of more: radix, in three launches and chained
+])
+def test_subkey_gradients_at_the_rule(gpu_lib, T, H, S, k):
+    """Both sorts at the lines of the rule that chooses between them."""
+    test_subkey_gradients_exact(gpu_lib, T, H, S, k, 0.05)
