@@ -324,9 +324,14 @@ bool split_plan(bool bf16, int64_t T, int H, int S, int k, SplitPlan* plan) {
     if (!fits(R)) return false;
   }
   const int parts = parts_of(R);
-  // one workgroup per CU of 16 waves, two of 8
-  const int64_t want = R >= 512 ? 256 : 512;
-  int64_t slices = (want + (int64_t)2 * H * parts - 1) / ((int64_t)2 * H * parts);
+  // One workgroup per CU of 16 waves, two of 8, and none beyond: a few more would
+  // run as a second round on nearly idle CUs (3 parts of 8 tables, 128 groups,
+  // k = 32: 122 us as 264 workgroups, 86 as 240).  With parts of 1024 rows, which
+  // are bound by their key reads, a short last part ends early and rounding up
+  // is better on the whole (8 tables, 32 groups, 264 / 192 workgroups: S = 2049 52
+  // / 63 us, S = 2500 57 / 65; but 64 groups of S = 3000 122 / 104).
+  const int64_t cus = R >= 512 ? 256 : 512, unit = (int64_t)2 * H * parts;
+  int64_t slices = R == 1024 ? (cus + unit - 1) / unit : cus / unit;
   if (slices > groups) slices = groups;
   if (slices < 1) slices = 1;
   const int64_t per = (groups + slices - 1) / slices;  // groups per workgroup, evened out
