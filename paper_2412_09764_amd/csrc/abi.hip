@@ -405,7 +405,7 @@ static int search_common(const char* fn, const void* q, pkmem_dtype q_dt, const 
   }
   int32_t* hidx = half_idx_out ? half_idx_out : w.half_idx;
   pk::SplitPlan plan{0, 0, 0, 0};  // parts = 0: half lists, no part records
-  if (pk::split_plan(bf16, T, H, S, k, &plan))
+  if (pk::split_plan(bf16, T, H, n, S, k, &plan))
     e = pk::launch_search_split(bf16, q, subkeys, T, H, n, S, k, qstats, has_sink ? sink : nullptr,
                                 w.sink_part, plan, w.cand, st);
   else

@@ -52,7 +52,7 @@ constexpr int SPLIT_PARTS_MAX = 16;
 struct SplitPlan {
   int rows, parts, cap, slices;
 };
-bool split_plan(bool bf16, int64_t T, int H, int S, int k, SplitPlan* plan);
+bool split_plan(bool bf16, int64_t T, int H, int n, int S, int k, SplitPlan* plan);
 // Leaves cap record slots per token and part in cand (the candidate runs).
 hipError_t launch_search_split(bool bf16, const void* q, const void* subkeys, int64_t T, int H,
                                int n, int S, int k, const float2* qstats, const void* sink,

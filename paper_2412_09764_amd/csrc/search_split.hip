@@ -298,6 +298,21 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
 //     against 130 at 32 tokens, 66 against 106 at 2000 (k_score_topk at its
 //     best workgroup size), 115 against 118 at 4000, 210 against 167 at 8000;
 //     S = 1024: 73 against 90 at 4000, 127 against 128 at 8000.
+//   * Few sub-keys: a part costs the same however few of its rows exist, so up to
+//     k = 36 at most 2^16 rows (S = 64, d = 64, split / many: 2^16 rows 70 / 74, 2^17
+//     126 / 96, 2^18 240 / 173; S = 256 71 / 86, 128 / 112; fp32 S = 32 83 / 80, 150 /
+//     106).
+//   * k from 37 to 56: more and more parts have over 64 records and take the exact
+//     cut, so rows * parts <= 2^16 up to k = 40 and in fp32 (k = 40: S = 2048, 2^14
+//     rows bf16 115 / 96, fp32 147 / 222; S = 1024, 2^15 rows 121 / 96, 154 / 162), 2^15
+//     else (k = 44, H = 4: S = 512 2^15 rows 101 / 91, 2^16 186 / 144; S = 1024 2^14 rows
+//     94 / 83, 2^15 167 / 106; S = 2048 2^13 rows 89 / 96, 2^14 162 / 108).  Past k = 56 the
+//     many-row kernel's threshold leaves so many records that it rescans (k = 60,
+//     S = 1024, 2^14 rows 115 / 211; k = 64, S = 512, 2^15 rows 128 / 1429).
+//   * Parts of 1024 rows read their keys from L2 for every group, so rows * parts *
+//     max(d, 128) <= 3072 * S (S = 2049, 3 parts: d = 64 12000 rows 60 / 71, 16000 90 / 73;
+//     d = 256 8192 rows 82 / 91, 10000 102 / 92; S = 4096, d = 256: 10000 rows 126 / 143,
+//     16000 195 / 147).
 //   * R = 512 where the call then still has a workgroup per CU (fewer records
 //     to merge: S = 1024, 2000 tokens 44 against 48), else 256 (32 tokens: 14
 //     against 16).  R = 128 gains nothing (T = 1: 12.5 against 11.7).
@@ -307,7 +322,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
 //     two tiles' fragments outgrow the registers), and past that, up to
 //     k = 32, slots for exactly the top k: S = 8192, 64 tokens 56 against 243,
 //     but 190 against 250 at 500 tokens, so only for rows * S < 2^25.
-bool split_plan(bool bf16, int64_t T, int H, int S, int k, SplitPlan* plan) {
+bool split_plan(bool bf16, int64_t T, int H, int n, int S, int k, SplitPlan* plan) {
   const int64_t work = T * H * 2 * S;
   if (work >= (int64_t)1 << 26) return false;
   const int slots = 32 * CAND_CAP / (T < 32 ? (int)T : 32);
@@ -324,6 +339,10 @@ bool split_plan(bool bf16, int64_t T, int H, int S, int k, SplitPlan* plan) {
     if (!fits(R)) return false;
   }
   const int parts = parts_of(R);
+  const int64_t rows = T * 2 * H;
+  const int64_t most = (int64_t)1 << (k <= 40 || !bf16 ? 16 : 15);
+  if (k <= 56 && rows * (k <= 36 ? 1 : parts) > most) return false;
+  if (R == 1024 && rows * parts * (n > 256 ? n / 2 : 128) > (int64_t)3072 * S) return false;
   // One workgroup per CU of 16 waves, two of 8, and none beyond: a few more would
   // run as a second round on nearly idle CUs (3 parts of 8 tables, 128 groups,
   // k = 32: 122 us as 264 workgroups, 86 as 240).  With parts of 1024 rows, which

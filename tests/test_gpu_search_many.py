@@ -51,3 +51,29 @@ def test_few_tokens_of_many_heads(gpu_lib, T, H):
     assert torch.equal(hidx.long(), hi)
     assert torch.equal(idx, want)
     assert torch.equal(score.double(), z.double())
+
+
+@pytest.mark.parametrize("T,H,d,S,k,dt", [
+    # few sub-keys of many rows: the last call of the path for few rows, the first past it
+    (16384, 2, 16, 64, 36, BF), (16385, 2, 16, 64, 36, BF), (33000, 1, 8, 8, 8, torch.float32),
+    (9000, 4, 32, 300, 20, BF),
+    # k from 37 to 56: 2^16 or 2^15 rows x parts and one token more; k = 57 stays
+    (8192, 2, 16, 513, 37, BF), (8193, 2, 16, 513, 37, BF), (4096, 2, 16, 513, 41, BF),
+    (4097, 2, 16, 513, 41, BF), (4100, 4, 64, 600, 56, torch.float32), (4097, 2, 16, 513, 57, BF),
+    # parts of 1024 rows: on the line and past it, by rows and by d
+    (4098, 2, 64, 2049, 32, BF), (4099, 2, 64, 2049, 32, BF), (2050, 2, 256, 2049, 16, BF),
+    (1500, 3, 160, 4096, 32, BF),
+])
+def test_both_sides_of_the_lines(gpu_lib, T, H, d, S, k, dt):
+    """Calls around the sizes at which the search changes its path."""
+    print(f"[lines] {T} {H} {d} {S} {k} {dt}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(600 + T)
+    q = torch.randint(-64, 65, (T, H, 2 * d), generator=g, device="cuda", dtype=torch.int8).to(dt)
+    K = torch.randint(-64, 65, (H, 2, S, d), generator=g, device="cuda", dtype=torch.int8).to(dt)
+    idx, w, score, hidx = pk.mem_search(q, K, k, want_half=True)
+    torch.cuda.synchronize()
+    hi, want, z = exact_search(q, K, k)
+    assert torch.equal(hidx.long(), hi)
+    assert torch.equal(idx, want)
+    assert torch.equal(score.double(), z.double())
+    assert (w - torch.softmax(z.double(), -1)).abs().max().item() <= 1e-5
