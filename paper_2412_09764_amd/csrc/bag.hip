@@ -513,10 +513,17 @@ hipError_t launch_bag_forward(bool bf16, const void* values, int D, const int64_
   // slabs (one wave per token against the split: D = 2048, 32 tokens 42 / 7.4
   // us, 512 55 / 48, 1024 89 / 91; D = 256, 1024 tokens 19 / 14, 2000 24 / 24)
   // and each wave's lane groups have lookups enough to be worth it (bag 8 at
-  // D = 64 fp32: 2.9 / 3.4).  Narrow rows take 4 waves (D = 64, 512 tokens:
-  // 5.0 against 5.6 with 8), others 8 (D = 2048, 1 token: 5.0 against 6.6).
+  // D = 64 fp32: 2.9 / 3.4), the more the more tokens there are, since one wave
+  // per token then fills the chip too (D = 256: bag 16 512 tokens 5.9 / 6.6, 2048 6.4 /
+  // 10.9; bag 32 1024 tokens 7.4 / 8.0, 2048 8.7 / 12.3; bag 64 1500 12.5 / 11.4.  D = 64:
+  // bag 64 1024 tokens 6.7 / 6.6, 1500 6.3 / 7.7; bag 128 9.2 / 8.0.  D = 1024, two slabs:
+  // bag 16 512 tokens 7.7 / 6.4, 1024 8.8 / 10.6; bag 32 14.6 / 13.9).
+  // Narrow rows take 4 waves (D = 64, 512 tokens: 5.0 against 5.6 with 8),
+  // others 8 (D = 2048, 1 token: 5.0 against 6.6).
   const int nslab = (C + 63) / 64;
-  if (T * nslab <= 2048 && (int64_t)bag * (C < 64 ? C : 64) >= 8 * WAVE) {
+  const int per_lookup = C > 64 ? 32 : C > 16 ? C : C > 8 ? 24 : 16;  // tokens per lookup of the bag
+  if (T * nslab <= 2048 && (int64_t)bag * (C < 64 ? C : 64) >= 8 * WAVE &&
+      T <= (int64_t)bag * per_lookup) {
     const dim3 grid((unsigned)(T * nslab));
 #define PK_SPLIT(CL)                                                                               \
   do {                                                                                             \

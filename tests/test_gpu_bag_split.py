@@ -74,3 +74,13 @@ def test_infinite_weight_stays_infinite(gpu_lib, T, bag, D, dt):
         y = pk.mem_bag_forward(V, idx, w)
         torch.cuda.synchronize()
         assert (y == float("inf")).all(), j
+
+
+@pytest.mark.parametrize("T,bag,D,dt", [
+    (1024, 64, 64, "bf16"), (1025, 64, 64, "bf16"), (768, 32, 128, "bf16"), (769, 32, 128, "bf16"),
+    (512, 16, 256, "bf16"), (513, 16, 256, "bf16"), (512, 8, 512, "bf16"), (513, 8, 512, "bf16"),
+    (512, 16, 1024, "bf16"), (513, 16, 1024, "bf16"), (256, 8, 2048, "f32"), (257, 8, 2048, "f32"),
+])
+def test_both_sides_of_the_token_line(gpu_lib, T, bag, D, dt):
+    """The last call of few tokens to a bag, and the next."""
+    test_bag_of_few_tokens(gpu_lib, T, bag, D, dt, False)
