@@ -446,7 +446,8 @@ def _search_overflow_count(q, K, k):
     overflow list, whose offset mirrors the workspace layout of csrc/abi.hip
     (candidate slots, run counts, thresholds, half lists, overflow list, each
     256-byte aligned; 256 candidate slots per (token, head, half) row, for
-    tokens rounded up to whole groups of 32)."""
+    tokens rounded up to whole groups of 32).  Only the path for many rows
+    counts, so the workspace starts as ones: a count that nobody wrote reads -1."""
     import paper_2412_09764_amd as pk
     T, H, n = q.shape
     S = K.shape[2]
@@ -454,10 +455,11 @@ def _search_overflow_count(q, K, k):
     grows = (T + 31) // 32 * 32 * H * 2
     a = lambda x: (x + 255) // 256 * 256  # noqa: E731
     off = a(grows * 256 * 8) + a(rows * 2 * 4) + a(rows * 4) + 2 * a(rows * k * 4)
-    ws = torch.zeros(pk.mem_search_workspace_size(T, H, S, k), dtype=torch.uint8, device="cuda")
+    ws = torch.full((pk.mem_search_workspace_size(T, H, S, k),), 255, dtype=torch.uint8, device="cuda")
     idx, w, score, hidx = pk.mem_search(q, K, k, want_half=True, workspace=ws)
     torch.cuda.synchronize()
     nov = int(ws[off:off + 4].view(torch.int32).item())
+    assert nov >= 0, "the call did not take the path for many rows"
     return idx, hidx, nov
 
 
@@ -466,8 +468,8 @@ def test_search_ties_but_one_needs_no_rescan(gpu_lib, k):
     """Every sub-key equal except one lower row: every score of a row ties but
     one.  The k lowest indices other than that row are selected, and no row
     goes to the exact rescan (a lane keeps at most k + 15 records per sweep
-    once it holds k at the threshold)."""
-    T, H, S, n = 512, 2, 2048, 64
+    once it holds k at the threshold).  8192 tokens: the path for many rows."""
+    T, H, S, n = 8192, 2, 2048, 64
     low = 5
     q = normal_tensor((T, H, n), 155, torch.float32).abs().to(torch.bfloat16).cuda()
     K = torch.full((H, 2, S, n // 2), 0.0625, dtype=torch.bfloat16, device="cuda")
@@ -499,7 +501,7 @@ def test_search_gaussian_records_per_row_bounded(gpu_lib):
     grows = (T + 31) // 32 * 32 * H * 2
     nruns = grows // 32
     off = (grows * 256 * 8 + 255) // 256 * 256
-    ws = torch.zeros(pk.mem_search_workspace_size(T, H, wl.S, wl.k), dtype=torch.uint8, device="cuda")
+    ws = torch.full((pk.mem_search_workspace_size(T, H, wl.S, wl.k),), 255, dtype=torch.uint8, device="cuda")
     pk.mem_search(q, K, wl.k, workspace=ws)
     torch.cuda.synchronize()
     per_row = int(ws[off:off + nruns * 4].view(torch.int32).sum().item()) / (T * H * 2)
