@@ -36,7 +36,7 @@ MFMA_F32_PEAK_TFLOPS = 157.3
 KERNELS = ["score_topk", "cartesian", "bag_forward", "sort_by_row", "bag_backward_rows",
            "bag_backward_atomic", "softmax_backward", "search_backward", "topk_sort"]
 KERNEL_SOURCES = {
-    "score_topk": ["search.hip", "pk_device.h"],
+    "score_topk": ["search.hip", "pk_mfma.h", "pk_device.h"],
     "topk_sort": ["search.hip", "pk_device.h"],
     "cartesian": ["search.hip", "pk_device.h"],
     "bag_forward": ["bag.hip", "pk_device.h"],

@@ -416,9 +416,9 @@ static int search_common(const char* fn, const void* q, pkmem_dtype q_dt, const 
     rc = check_indices(fn, ex_idx, T * H * nex, (int64_t)S * S, st);
     if (rc) return rc;
   }
-  e = pk::launch_cartesian(hidx, w.half_score, w.cand, plan, half_idx_out, T, H, S, k, bf16, q, subkeys, n, ex_idx, nex,
-                           has_sink ? w.sink_part : nullptr, sink_row0, idx_out, w_out, score_out,
-                           st);
+  e = pk::launch_cartesian(hidx, w.half_score, w.cand, plan, half_idx_out, T, H, S, k, bf16, q,
+                           subkeys, n, ex_idx, nex, has_sink ? w.sink_part : nullptr, sink_row0,
+                           idx_out, w_out, score_out, st);
   if (e != hipSuccess) return hip_status(e, fn);
   return PKMEM_OK;
 }

@@ -26,6 +26,7 @@ class LaunchTimer {
 // the per-row sort of the search; the 32 rows of a scoring wave share one run
 // of 32 * CAND_CAP records.
 constexpr int CAND_CAP = 256;
+
 // Number of (i1, i2) rank pairs with (i1 + 1) * (i2 + 1) <= k: only these can
 // reach the top k of the k*k sums when both half lists are sorted.
 int cartesian_pairs(int k);
@@ -34,8 +35,7 @@ int cartesian_pairs(int k);
 // rows = T*H*2 (token, head, half) rows; cand = one run of 32 * CAND_CAP u64
 // records per group of 32 tokens, head and half (ceil(T / 32) * H * 2 runs);
 // cnts = [rows, 2] u32 (records per run, in its first entries); thr = [rows]
-// fp32 (each row's
-// final threshold: no score below it can be selected);
+// fp32 (each row's final threshold: no score below it can be selected);
 // ovf = [1 + rows] u32 (count, then overflowed row ids).
 // qstats (nullable) = per (token, head) query (mean, rstd): the scoring then
 // normalises the queries as it loads them (see launch_qnorm).
@@ -68,7 +68,8 @@ hipError_t launch_qnorm(bool bf16, const void* q, int64_t rows, int n, float eps
 // parts > 0: the half lists come from the part records of launch_search_split
 // (half_idx and half_score are not read) and go to half_out unless null.
 hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, const uint64_t* recs,
-                            const SplitPlan& plan, int32_t* half_out, int64_t T, int H, int S, int k, bool bf16, const void* q, const void* subkeys, int n,
+                            const SplitPlan& plan, int32_t* half_out, int64_t T, int H, int S,
+                            int k, bool bf16, const void* q, const void* subkeys, int n,
                             const int64_t* ex_idx, int nex, const float* sink_part,
                             int64_t sink_row0, int64_t* idx_out, float* w_out, float* score_out,
                             hipStream_t st);

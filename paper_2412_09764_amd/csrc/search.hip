@@ -1343,10 +1343,11 @@ static void cart_launch(dim3 g, dim3 b, hipStream_t st, const CartIn& in, int64_
 }
 
 hipError_t launch_cartesian(const int32_t* half_idx, const float* half_score, const uint64_t* recs,
-                            const SplitPlan& plan, int32_t* half_out, int64_t T_, int H, int S, int k, bool bf16,
-                            const void* q, const void* subkeys, int n, const int64_t* ex_idx,
-                            int nex, const float* sink_part, int64_t sink_row0, int64_t* idx_out,
-                            float* w_out, float* score_out, hipStream_t st) {
+                            const SplitPlan& plan, int32_t* half_out, int64_t T_, int H, int S,
+                            int k, bool bf16, const void* q, const void* subkeys, int n,
+                            const int64_t* ex_idx, int nex, const float* sink_part,
+                            int64_t sink_row0, int64_t* idx_out, float* w_out, float* score_out,
+                            hipStream_t st) {
   const int64_t rows = T_ * H;
   const int np = cartesian_pairs(k);
   int64_t blocks = (rows + 3) / 4;

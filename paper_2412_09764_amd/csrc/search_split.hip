@@ -34,7 +34,7 @@ namespace pk {
 constexpr int SPLIT_RECS = 64;  // record slots per token and part
 
 template <typename T, int NSTEP, int W, int TPW>
-__global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
+__global__ __launch_bounds__(64 * W, 4) void k_score_split(
     const T* __restrict__ q, const T* __restrict__ subkeys, int64_t ntok, int H, int n, int S,
     int k, const float2* __restrict__ qstats, const T* __restrict__ sink,
     float* __restrict__ sink_part, int parts, int cap, int slices, uint64_t* __restrict__ cand) {
@@ -291,9 +291,9 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 4) void k_score_split(
   }
 }
 
-// Sub-keys per part, record slots per token and part, and how many workgroups
-// share a part; measured at H = 4, n = 512, k = 32 in bf16 (whole searches in
-// us, as HIP graphs).
+// Which calls take this path, the sub-keys per part, the record slots per token
+// and part, and how many workgroups share a part (whole searches in us, as HIP
+// graphs; bf16, H = 4, n = 512, k = 32 where nothing else is said; rows = T * 2H).
 //   * rows * S < 2^26: below it the split is the faster path.  S = 2048: 16
 //     against 130 at 32 tokens, 66 against 106 at 2000 (k_score_topk at its
 //     best workgroup size), 115 against 118 at 4000, 210 against 167 at 8000;

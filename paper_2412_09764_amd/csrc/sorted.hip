@@ -8,7 +8,8 @@
 //      contiguous quarter of the tile with ballots, and the tile goes out
 //      through LDS in sorted order.  Keys are rows (< 2^26), values lookup ids.
 //      For fewer keys the passes are a short chain instead (k_chain_*), up to
-//      8192 one workgroup does everything (k_sort_one).
+//      8192 one workgroup does everything (k_sort_one).  The search backward
+//      sorts its slots with the same passes.
 //   2. Segment heads (first lookup of each distinct row) -> seg_start[U + 1],
 //      the head flags computed where they are counted and placed; the same
 //      kernel lists the segments longer than a threshold.
@@ -21,10 +22,11 @@
 //      value and gradient tables are streamed nearly sequentially, and the
 //      result is bitwise deterministic.
 //   4. A row with more than LONG_SEG lookups would hold one lane group for
-//      its whole length: it is listed, the per-row kernel skips it,
-//      and a second kernel gives each listed row a workgroup whose lane
-//      groups take contiguous runs of its lookups; their partial sums meet in
-//      LDS and are added in group order (still deterministic).
+//      its whole length: it is listed, the per-row kernel skips it, and it is
+//      cut into chunks of consecutive lookups, each summed by a workgroup of
+//      its own whose lane groups take contiguous runs of the chunk (their
+//      partial sums meet in LDS); a last kernel adds the chunks' partial rows
+//      in chunk order (still deterministic).
 #include "pk_device.h"
 #include "pk_internal.h"
 
