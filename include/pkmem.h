@@ -65,8 +65,11 @@ typedef enum {
 /* Value-gradient strategies of the EmbeddingBag backward (Sec. 3.1.4). */
 typedef enum {
   PKMEM_BWD_AUTO = 0,   /* library's choice: atomic when T*H*k*D <= 2^26 and
-                           D <= 1024 (small batches), sorted otherwise
-                           (measured crossover on MI355X)                      */
+                           D <= 1024 (small batches), sorted otherwise.  The
+                           line is fixed, as workspaces and the order of sums
+                           depend on it; it follows a crossover measured on
+                           MI355X, but near it, with D of 512 and more, sorted
+                           is the faster one by 9 to 11%: ask for it there     */
   PKMEM_BWD_ATOMIC = 1, /* fp32 atomic adds straight into grad_values          */
   PKMEM_BWD_SORTED = 2  /* lookups sorted by row, one read-modify-write per
                            touched row, contributors summed in lookup order:

@@ -129,10 +129,12 @@ size_t bwd_ws_bytes(int64_t T, int H, int k, int D, int mode) {
 // up to 2^19 lookups one per pass) plus its row streaming, so atomics win only
 // small batches: D = 64, 524288 lookups 0.11 against 0.16 ms, but D = 128,
 // 1048576 lookups 0.44 against 0.38.  At D = 2048 the sort wins from 256 tokens
-// on.  The line is part of the interface (pkmem.h); at its upper edge for D of
-// 512 and more the sort is by now up to 11% the faster one (D = 1024, 32768
-// lookups 0.137 against 0.122 ms).  PKMEM_BWD_MODE=atomic|sorted in
-// the environment overrides the choice (read at every call).
+// on.  The line is fixed in the interface (pkmem.h states it: workspaces are sized
+// and the sum's order, bitwise deterministic or not, is chosen by it); at its upper edge
+// for D of 512 and more the sort is the faster one by 9 to 11% (D = 512, 131072
+// lookups 0.229 against 0.208 ms; D = 1024, 32768 0.137 against 0.122).
+// PKMEM_BWD_MODE=atomic|sorted in the environment overrides the choice (read at
+// every call).
 int resolve_mode(int mode, int D, int64_t L) {
   if (mode != PKMEM_BWD_AUTO) return mode;
   const char* env = getenv("PKMEM_BWD_MODE");

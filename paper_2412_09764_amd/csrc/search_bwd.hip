@@ -212,8 +212,8 @@ struct Seg16<float> {
 // is done once instead of twice (with 32-bit masks), and a sub-key row is read
 // by 32 lanes of 16 bytes, a row of each half per instruction.  The kernel is
 // bound by its vector instructions, not by the row reads from L2: 1052 per wave
-// and 231 us as two passes (32768 tokens, 4 heads, S = 2048, k = 32), 694 and
-// 176 us like this.  Every sum is the other form's, in its order.
+// and 231 us as two passes (32768 tokens, 4 heads, S = 2048, k = 32), 709 and
+// 177 us like this.  Every sum is the other form's, in its order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_search_bwd_q32(
     const T* __restrict__ q, const T* __restrict__ subkeys, int64_t ntok, int H, int n, int S,
@@ -359,8 +359,7 @@ __global__ __launch_bounds__(256) void k_search_bwd_q32(
 // it (neither non-temporal reads nor reading a batch ahead changed that).  A scan
 // of the counts, a packing of the leaders, two radix passes and the marking of
 // segments in 13 launches took 157, and left the sums another gather (221 us
-// with it, 179 without).  Whole search backward 546 -> 454 us; training steps with
-// it: 16384 tokens 3240 -> 3175, 3001 tokens 480 -> 461, 512 tokens 389 -> 373.
+// with it, 179 without).
 constexpr uint32_t SBWD_LONG = 2048;  // pairs of a sub-key beyond which k_sbwd_long sums them
 constexpr int BIN_U = 16;             // rows in flight per wave
 
@@ -613,7 +612,8 @@ __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, 
   // the segments (with 2H = 8 one head's half), whose waves walk the tokens at
   // about the same pace, so that a query half read for one sub-key is still in
   // the XCD's L2 for the others its token chose (245 -> 222 us at 32768 tokens,
-  // 4 heads, S = 2048; 31% of the requests hit, as the paces drift apart).
+  // 4 heads, S = 2048, and 178 with the counting sort's pairs; 36% of the requests
+  // hit against 18%, no more as the paces drift apart).
   const uint32_t per = (nseg + 7u) / 8u;
   const uint32_t u0 = (blockIdx.x & 7u) * per;
   const uint32_t u1 = u0 + per < nseg ? u0 + per : nseg;
