@@ -291,6 +291,36 @@ __global__ __launch_bounds__(64 * W, 4) void k_score_split(
   }
 }
 
+// The most rows (T * 2H) for which the path is taken, besides rows * S < 2^26
+// (split / many as ratios of whole searches, over d 8 to 256 and both dtypes):
+//   * up to k = 36, by the sub-keys: a part costs the same however few of its rows
+//     exist, while the many-row kernel fills the chip from 2^15 to 2^17 rows in
+//     three steps, whatever S.  k = 8: S = 64 2^15 rows 1.08-1.19, 2^17 1.43-1.57; S = 128
+//     2^15 0.99-1.05, 2^16 1.06-1.14; S = 256 70000 0.87-0.98, 90000 0.98-1.07; S = 400 90000
+//     0.80-0.97, 2^17 1.02-1.19.  k = 32: S = 64 2^16 0.93-1.04, 90000 1.05-1.14; S = 128
+//     90000 0.95-1.02, 2^17 1.17-1.27; S = 400 2^17 0.99-1.10.
+//   * from there to k = 56 more and more parts have over 64 records and take the
+//     exact cut, so the rows are counted once per part.  k = 40: S = 128 90000 0.90-0.97;
+//     S = 1024 2^15 rows 121 / 96 us, fp32 154 / 162; S = 2048 2^14 rows 115 / 96, fp32 147 /
+//     222.  k = 44: S = 512 2^15 101 / 91, 2^16 186 / 144; S = 1024 2^14 94 / 83, 2^15 167 / 106;
+//     S = 2048 2^13 89 / 96, 2^14 162 / 108.
+//   * past k = 56 the many-row kernel's threshold leaves so many records that it
+//     rescans (k = 60, S = 1024, 2^14 rows 115 / 211 us; k = 64, S = 512, 2^15 128 / 1429),
+//     but not of 256 sub-keys or fewer (k = 64: S = 64 90000 0.80-0.86, S = 128 2^16 0.99-1.02,
+//     90000 1.22-1.25; S = 256 90000 0.95-0.98).
+static int64_t split_rows_max(bool bf16, int S, int k, int parts) {
+  if (k <= 16) {
+    if (S <= 128) return 1 << 15;
+    if (S <= 256) return k > 4 ? 5 << 14 : 1 << 16;
+    return k > 8 ? 7 << 14 : 3 << 15;
+  }
+  if (k <= 36) return S <= 64 ? 1 << 16 : S <= 256 ? 3 << 15 : 1 << 17;
+  if (k <= 40) return S <= 256 ? 3 << 15 : (1 << 16) / parts;
+  if (k <= 56) return (bf16 ? 1 << 15 : 1 << 16) / parts;
+  if (S <= 256) return S > 64 && S <= 128 ? 1 << 16 : 3 << 15;
+  return INT64_MAX;
+}
+
 // Which calls take this path, the sub-keys per part, the record slots per token
 // and part, and how many workgroups share a part (whole searches in us, as HIP
 // graphs; bf16, H = 4, n = 512, k = 32 where nothing else is said; rows = T * 2H).
@@ -298,17 +328,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_score_split(
 //     against 130 at 32 tokens, 66 against 106 at 2000 (k_score_topk at its
 //     best workgroup size), 115 against 118 at 4000, 210 against 167 at 8000;
 //     S = 1024: 73 against 90 at 4000, 127 against 128 at 8000.
-//   * Few sub-keys: a part costs the same however few of its rows exist, so up to
-//     k = 36 at most 2^16 rows (S = 64, d = 64, split / many: 2^16 rows 70 / 74, 2^17
-//     126 / 96, 2^18 240 / 173; S = 256 71 / 86, 128 / 112; fp32 S = 32 83 / 80, 150 /
-//     106).
-//   * k from 37 to 56: more and more parts have over 64 records and take the exact
-//     cut, so rows * parts <= 2^16 up to k = 40 and in fp32 (k = 40: S = 2048, 2^14
-//     rows bf16 115 / 96, fp32 147 / 222; S = 1024, 2^15 rows 121 / 96, 154 / 162), 2^15
-//     else (k = 44, H = 4: S = 512 2^15 rows 101 / 91, 2^16 186 / 144; S = 1024 2^14 rows
-//     94 / 83, 2^15 167 / 106; S = 2048 2^13 rows 89 / 96, 2^14 162 / 108).  Past k = 56 the
-//     many-row kernel's threshold leaves so many records that it rescans (k = 60,
-//     S = 1024, 2^14 rows 115 / 211; k = 64, S = 512, 2^15 rows 128 / 1429).
+//   * split_rows_max above.
 //   * Parts of 1024 rows read their keys from L2 for every group, so rows * parts *
 //     max(d, 128) <= 3072 * S (S = 2049, 3 parts: d = 64 12000 rows 60 / 71, 16000 90 / 73;
 //     d = 256 8192 rows 82 / 91, 10000 102 / 92; S = 4096, d = 256: 10000 rows 126 / 143,
@@ -340,8 +360,7 @@ bool split_plan(bool bf16, int64_t T, int H, int n, int S, int k, SplitPlan* pla
   }
   const int parts = parts_of(R);
   const int64_t rows = T * 2 * H;
-  const int64_t most = (int64_t)1 << (k <= 40 || !bf16 ? 16 : 15);
-  if (k <= 56 && rows * (k <= 36 ? 1 : parts) > most) return false;
+  if (rows > split_rows_max(bf16, S, k, parts)) return false;
   if (R == 1024 && rows * parts * (n > 256 ? n / 2 : 128) > (int64_t)3072 * S) return false;
   // One workgroup per CU of 16 waves, two of 8, and none beyond: a few more would
   // run as a second round on nearly idle CUs (3 parts of 8 tables, 128 groups,

@@ -64,8 +64,11 @@ def test_few_tokens_of_many_heads(gpu_lib, T, H):
 
 @pytest.mark.parametrize("T,H,d,S,k,dt", [
     # few sub-keys of many rows: the last call of the path for few rows, the first past it
-    (16384, 2, 16, 64, 36, BF), (16385, 2, 16, 64, 36, BF), (33000, 1, 8, 8, 8, torch.float32),
-    (9000, 4, 32, 300, 20, BF),
+    (8192, 2, 16, 100, 16, BF), (8193, 2, 16, 100, 16, BF), (33000, 1, 8, 8, 8, torch.float32),
+    (20480, 2, 16, 200, 9, BF), (20481, 2, 16, 200, 9, BF), (12288, 4, 8, 300, 5, BF), (12289, 4, 8, 300, 5, BF),
+    (16384, 2, 16, 64, 36, BF), (16385, 2, 16, 64, 36, BF), (24577, 2, 16, 70, 17, torch.float32),
+    (16385, 4, 8, 300, 20, BF), (24576, 2, 16, 130, 40, BF), (24577, 2, 16, 130, 40, BF),
+    (16384, 2, 16, 100, 64, BF), (16385, 2, 16, 100, 64, BF), (24577, 2, 16, 200, 64, BF),
     # k from 37 to 56: 2^16 or 2^15 rows x parts and one token more; k = 57 stays
     (8192, 2, 16, 513, 37, BF), (8193, 2, 16, 513, 37, BF), (4096, 2, 16, 513, 41, BF),
     (4097, 2, 16, 513, 41, BF), (4100, 4, 64, 600, 56, torch.float32), (4097, 2, 16, 513, 57, BF),
