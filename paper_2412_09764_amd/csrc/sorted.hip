@@ -1170,7 +1170,9 @@ __global__ __launch_bounds__(REDUCE_THREADS) void k_long_reduce(
       float* dst = (SPARSE ? grad_rows_out + (size_t)u * D : grad_values + row * D) + (size_t)qd * 4;
       float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
       if (dense) tot = *reinterpret_cast<const float4*>(dst);
-      for (int j = 0; j < ng; ++j) {
+      // the groups with partial rows (narrow rows: up to 512 groups, often fewer rows)
+      const int used = (int)((cnt + per - 1) / per);
+      for (int j = 0; j < used; ++j) {
         const float4 pv = run[j * nquad + qd];
         tot.x += pv.x; tot.y += pv.y; tot.z += pv.z; tot.w += pv.w;
       }

@@ -136,3 +136,26 @@ def test_row_chosen_by_most_tokens(gpu_lib):
     assert normwise(h64(grows[hot_u]), ref["grad_rows"][hot_u]) <= TOL_F32
     assert normwise(h64(gv[torch.from_numpy(ref["rows"]).cuda()]), ref["grad_rows"]) <= TOL_F32
     assert normwise(h64(gw), ref["grad_w"]) <= TOL_F32
+
+
+@pytest.mark.parametrize("T,N,D", [(40000, 13, 8), (5000, 1, 8), (30000, 3, 64), (9000, 2, 2048)])
+def test_few_partial_rows_of_narrow_rows(gpu_lib, T, N, D):
+    """Long rows whose chunks are fewer than the reduction's thread groups, and
+    more (D = 2048: two groups); whole numbers, so the sums are exact."""
+    print(f"[long-few] {T} {N} {D}", flush=True)
+    g = torch.Generator().manual_seed(801 + T)
+    idx = torch.randint(0, N, (T, 1, 2), generator=g).cuda()
+    w = torch.randint(-2, 3, (T, 1, 2), generator=g).float().cuda()
+    dy = torch.randint(-2, 3, (T, D), generator=g).to(torch.bfloat16).cuda()
+    V = torch.randint(-2, 3, (N, D), generator=g).to(torch.bfloat16).cuda()
+    base = torch.randint(-9, 10, (N, D), generator=g).float().cuda()
+    gv, gw, _ = gpu_lib.mem_bag_backward(dy, V, idx, w, grad_values=base.clone(), mode="sorted")
+    rows, gr, _, _ = gpu_lib.mem_bag_backward_sparse(dy, V, idx, w)
+    torch.cuda.synchronize()
+    want = torch.zeros((N, D), device="cuda")
+    for j in range(2):
+        hot = torch.nn.functional.one_hot(idx[:, 0, j], N).float() * w[:, 0, j, None]
+        want += (hot.double().t().contiguous() @ dy.double()).float()
+    assert torch.equal(gv, base + want)
+    assert torch.equal(gr, want[rows])
+    assert torch.equal(gw[:, 0], (dy.float()[:, None] * V[idx[:, 0]].float()).sum(-1))
