@@ -238,9 +238,12 @@ __device__ __forceinline__ uint64_t make_key(float score, uint32_t index) {
 __device__ __forceinline__ float key_score(uint64_t key) { return ordered_to_f32(uint32_t(key >> 32)); }
 __device__ __forceinline__ uint32_t key_index(uint64_t key) { return ~uint32_t(key); }
 // The same for an entry of a half list: a row with fewer than k scores that are
-// numbers ends in empty keys, and these name row 0 (their score is NaN), so that
-// every index composed of half lists lies in the table.
-__device__ __forceinline__ uint32_t key_row(uint64_t key) { return key ? ~uint32_t(key) : 0u; }
+// numbers ends in empty keys, whose index reads -1, and these name row 0 (their
+// score is NaN), so that every index composed of half lists lies in the table.
+__device__ __forceinline__ int key_row(uint64_t key) {
+  const int i = (int)~uint32_t(key);
+  return i > 0 ? i : 0;
+}
 
 // ---------------------------------------------------------- shuffles ----
 // Value of lane (lane ^ MASK) for a constant MASK.  Distances 1 and 2 are DPP

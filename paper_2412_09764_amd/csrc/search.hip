@@ -696,7 +696,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_score_topk(
   sweep(0, P1, collect_tile);
   // The last tile's waves past the tokens have no run: search_ws holds a count
   // per 32 tokens only, and the thresholds follow it.
-  if (lane == 0 && tile * (32 * W) + wave * 32 < ntok) cnts[wr] = wcnt;
+  if (lane == 0 && tok_ok) cnts[wr] = wcnt;
 }
 
 // Pass 3 as a kernel of its own: one workgroup per wave run (32 tokens of one
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(256) void k_topk_sort(const uint64_t* __restrict__ 
     };
     auto write_top = [&](size_t r, uint64_t top) PK_INLINE {
       if (lane < k) {
-        half_idx[r * k + lane] = (int32_t)key_row(top);
+        half_idx[r * k + lane] = key_row(top);
         half_score[r * k + lane] = key_score(top);
       }
     };
@@ -1162,8 +1162,8 @@ __global__ __launch_bounds__(256) void k_cartesian(const int32_t* __restrict__ h
       merge_parts<EM>(rec, nrec, k, lane, stage[EM > 1 ? wave : 0], top);
       s1v = lane < k ? key_score(top[0]) : 0.f;
       s2v = lane < k ? key_score(top[1]) : 0.f;
-      i1v = lane < k ? (int)key_row(top[0]) : 0;
-      i2v = lane < k ? (int)key_row(top[1]) : 0;
+      i1v = lane < k ? key_row(top[0]) : 0;
+      i2v = lane < k ? key_row(top[1]) : 0;
       if (half_out && lane < k) {
         half_out[(size_t)row * 2 * k + lane] = i1v;
         half_out[(size_t)row * 2 * k + k + lane] = i2v;
