@@ -613,7 +613,7 @@ __global__ __launch_bounds__(256) void k_sbwd_segments(const T* __restrict__ q, 
   // about the same pace, so that a query half read for one sub-key is still in
   // the XCD's L2 for the others its token chose (245 -> 222 us at 32768 tokens,
   // 4 heads, S = 2048, and 178 with the counting sort's pairs; 36% of the requests
-  // hit against 18%, no more as the paces drift apart).
+  // hit against 19%, no more as the paces drift apart).
   const uint32_t per = (nseg + 7u) / 8u;
   const uint32_t u0 = (blockIdx.x & 7u) * per;
   const uint32_t u1 = u0 + per < nseg ? u0 + per : nseg;
